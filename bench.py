@@ -77,11 +77,13 @@ def log(msg: str):
 # the sources the standalone-solve kernels are compiled from, the dispatch
 # table that picks them and the compile flags: counters taken on other
 # sources do not describe the kernels this run launches
-KERNEL_SOURCES = ("include/lupp.h", "include/lupp_device.h",
+KERNEL_SOURCES = ("include/lupp.h", "include/lupp_device.h", "include/lupp_segments.h",
                   "paper_2609_15217_amd/csrc/internal.h",
                   "paper_2609_15217_amd/csrc/kernels_thread.h",
                   "paper_2609_15217_amd/csrc/kernels_lanes.h",
                   "paper_2609_15217_amd/csrc/kernels_lanes_soa.h",
+                  "paper_2609_15217_amd/csrc/kernels_seg.h",
+                  "paper_2609_15217_amd/csrc/kernels_seg_soa.h",
                   "paper_2609_15217_amd/dispatch_gfx950.json")
 
 

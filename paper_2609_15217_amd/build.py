@@ -53,6 +53,10 @@ def lanes_widths(n: int) -> list[int]:
 
 LANES = [(n, t) for n in range(2, 33) for t in lanes_widths(n)]
 
+# half the narrowest lanes width, for large solve-only and interleaved batches
+# (the dispatcher's own choice): strict and FMA kernels
+NARROW = [(n, 4) for n in range(9, 13)] + [(n, 8) for n in range(17, 25)]
+
 
 def _write_if_changed(path: str, text: str):
     if os.path.exists(path) and open(path).read() == text:
@@ -70,7 +74,11 @@ def generate(gen: str) -> list[str]:
         srcs.append(p)
     for n, t in LANES:
         p = os.path.join(gen, f"lanes_{n}_{t}.hip")
-        _write_if_changed(p, f'#include "kernels_lanes.h"\n#include "kernels_lanes_soa.h"\nLUPP_LANES_INSTANCE({n}, {t})\n')
+        _write_if_changed(p, f'#include "kernels_lanes.h"\nLUPP_LANES_INSTANCE({n}, {t})\n')
+        srcs.append(p)
+    for n, t in NARROW:
+        p = os.path.join(gen, f"narrow_{n}_{t}.hip")
+        _write_if_changed(p, f'#include "kernels_lanes.h"\nLUPP_NARROW_INSTANCE({n}, {t})\n')
         srcs.append(p)
     for g in range(4):
         ns = [n for n in range(1, 33) if (n - 1) % 4 == g]
@@ -89,6 +97,11 @@ def generate(gen: str) -> list[str]:
         lines.append(f"LaunchFn thread_fn_{n}(); const void *thread_sym_{n}();")
     for n, t in LANES:
         lines.append(f"LaunchFn lanes_fn_{n}_{t}(); const void *lanes_sym_{n}_{t}(int layout);")
+    for n, t in NARROW:
+        lines.append(f"LaunchFn narrow_fn_{n}();")
+    lines.append("LaunchFn narrow_launcher(int n) {\n  switch (n) {")
+    lines += [f"  case {n}: return narrow_fn_{n}();" for n, t in NARROW]
+    lines.append("  default: return nullptr;\n  }\n}")
     lines.append("LaunchFn thread_launcher(int n) {\n  switch (n) {")
     lines += [f"  case {n}: return thread_fn_{n}();" for n in THREAD_NS]
     lines.append("  default: return nullptr;\n  }\n}")
@@ -226,8 +239,8 @@ def build(jobs: int | None = None, force: bool = False, verbose: bool = True) ->
 
 def _weight(src: str) -> int:
     b = os.path.basename(src)
-    if b.startswith("lanes_"):
-        n, t = (int(v) for v in b[6:-4].split("_"))
+    if b.startswith(("lanes_", "narrow_")):
+        n, t = (int(v) for v in b[:-4].split("_")[1:])
         return n * n * ((n + t - 1) // t)
     if b.startswith("thread_"):
         n = int(b[7:-4])

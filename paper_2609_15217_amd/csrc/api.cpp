@@ -11,10 +11,14 @@
 namespace lupp {
 
 struct Choice {
-    int variant;  /* LUPP_VARIANT_THREAD / LUPP_VARIANT_LANES */
+    int variant;  /* LUPP_VARIANT_THREAD / LUPP_VARIANT_LANES / kVariantNarrow */
     int lanes;
     int wpb;
 };
+
+/* The lanes solver with half the lanes (twice the rows per lane) of the
+ * variants lupp_force_variant names: chosen by auto_choice only. */
+constexpr int kVariantNarrow = 3;
 
 }  // namespace lupp
 
@@ -24,6 +28,7 @@ struct lupp_ctx {
     int forced_lanes = 0;
     int forced_wpb = 0;
     lupp::Choice table[33][2][2]; /* [n][layout][batch bucket] */
+    bool chosen[33][2][2] = {};   /* entries the caller set or autotuned */
     lupp::RaggedWs *ragged_ws = nullptr; /* device workspace of the ragged path */
     lupp::BnWs *bn_ws = nullptr;         /* device workspace of the batched Newton */
     int newton_lanes[2] = {lupp::newton_default_lanes(LUPP_LAW_NORTON7),
@@ -75,7 +80,37 @@ static LaunchFn pick(int n, const Choice &c)
 {
     if (c.variant == LUPP_VARIANT_THREAD) return thread_launcher(n);
     if (c.variant == LUPP_VARIANT_LANES) return lanes_launcher(n, c.lanes);
+    if (c.variant == kVariantNarrow) return narrow_launcher(n);
     return nullptr;
+}
+
+/* Refinement of a built-in table entry by what the table does not hold: large
+ * batches that only solve (LUPP_KEEP_A). The table is tuned with the factors
+ * written, where stores of whole lines decide and more lanes per system win;
+ * without them instructions decide, and fewer lanes with more rows each spend
+ * fewer per system. Measured at 2^20 systems (n <= 16) and 2^18 (above), us,
+ * solve-only, table entry -> this one:
+ *   AoS  n = 3: 30.7 -> 24.4 (thread); n = 8: 156 -> 136, n = 5: 86.8 -> 64.2
+ *        (4 lanes); n = 12: 392 -> 289 (4 lanes, 3 rows each); n = 16: 667 ->
+ *        618 (8 lanes against 16); n = 24: 555 -> 435 (8 lanes, 3 rows each);
+ *        n = 32 at 2^20: 3538 -> 3425 (2 waves per workgroup against 4)
+ *   SoA  n = 12: 466 -> 335 (4 lanes against the thread kernel, which wins up
+ *        to n = 10: 225 against 247); n = 24: 654 -> 529
+ * The interleaved layout stores whole lines with any segment width, so 8 lanes
+ * also win there with the factors (n = 24: 767 -> 711; n = 17: 421 -> 353). */
+static Choice auto_choice(int n, int layout, int bucket, bool factors, const Choice &c)
+{
+    if (bucket == 0) return c;
+    const bool aos = layout == LUPP_AOS;
+    if (n >= 17 && n <= 24 && (!aos || !factors)) return {kVariantNarrow, 8, 1};
+    if (factors) return c;
+    if (!aos) return (n == 11 || n == 12) ? Choice{kVariantNarrow, 4, 0} : c;
+    if (n == 2 || n == 3) return {LUPP_VARIANT_THREAD, 1, 1};
+    if (n >= 5 && n <= 8) return {LUPP_VARIANT_LANES, 4, 2};
+    if (n >= 9 && n <= 12) return {kVariantNarrow, 4, 2};
+    if (n >= 13 && n <= 16) return {LUPP_VARIANT_LANES, 8, 4};
+    if (n >= 27) return {LUPP_VARIANT_LANES, 16, 2};
+    return c;
 }
 
 void ctx_copy_settings(lupp_ctx *dst, const lupp_ctx *src)
@@ -84,6 +119,7 @@ void ctx_copy_settings(lupp_ctx *dst, const lupp_ctx *src)
     dst->forced_lanes = src->forced_lanes;
     dst->forced_wpb = src->forced_wpb;
     std::memcpy(dst->table, src->table, sizeof(dst->table));
+    std::memcpy(dst->chosen, src->chosen, sizeof(dst->chosen));
     dst->newton_lanes[0] = src->newton_lanes[0];
     dst->newton_lanes[1] = src->newton_lanes[1];
     dst->tile = src->tile;
@@ -180,6 +216,7 @@ int lupp_set_dispatch(lupp_ctx *ctx, int n, int layout, int64_t batch, int varia
     if (pick(n, c) == nullptr) return -6;
     if (wpb != 0 && wpb != 1 && wpb != 2 && wpb != 4) return -7;
     ctx->table[n][layout][bucket_of(batch)] = c;
+    ctx->chosen[n][layout][bucket_of(batch)] = true;
     return 0;
 }
 
@@ -228,8 +265,14 @@ int lupp_batched_solve(lupp_ctx *ctx, int n, int64_t batch, int layout, double *
     /* compiled instances: strict, FMA, strict with tile-local pivoting */
     if ((flags & LUPP_FMA) != 0 && ctx->tile > 0) return LUPP_E_UNSUPPORTED;
     Choice c = ctx->table[n][layout][bucket_of(batch)];
-    if (ctx->forced_variant != LUPP_VARIANT_AUTO)
+    if (ctx->forced_variant != LUPP_VARIANT_AUTO) {
         c = Choice{ctx->forced_variant, ctx->forced_lanes, ctx->forced_wpb};
+    } else if (ctx->tile == 0 && !ctx->chosen[n][layout][bucket_of(batch)]) {
+        /* only where its address range holds too: strides beyond it keep the
+         * table's entry */
+        const Choice r = auto_choice(n, layout, bucket_of(batch), (flags & LUPP_KEEP_A) == 0, c);
+        if (fits_offsets(n, batch, layout, r.variant, r.lanes, strideA, strideB)) c = r;
+    }
     LaunchFn fn = pick(n, c);
     if (fn == nullptr) return LUPP_E_UNSUPPORTED;
     if (!fits_offsets(n, batch, layout, c.variant, c.lanes, strideA, strideB)) {
@@ -433,6 +476,7 @@ int lupp_autotune(lupp_ctx *ctx, int n, int64_t batch, int layout, const double 
     }
     if (rc == 0 && best.variant != 0) {
         ctx->table[n][layout][bucket_of(batch)] = best;
+        ctx->chosen[n][layout][bucket_of(batch)] = true;
         if (variant) *variant = best.variant;
         if (lanes) *lanes = best.lanes;
         if (wpb) *wpb = best.wpb;

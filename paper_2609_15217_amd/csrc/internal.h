@@ -32,6 +32,9 @@ typedef hipError_t (*LaunchFn)(const SolveArgs &, int layout, bool factors, int 
 /* Kernel lookup (registry.cpp): nullptr if the variant is not compiled. */
 LaunchFn thread_launcher(int n);
 LaunchFn lanes_launcher(int n, int lanes);
+/* the lanes solver at half the narrowest width of lanes_launcher (9..12: 4,
+ * 17..24: 8 lanes): strict and FMA arithmetic, textbook pivoting */
+LaunchFn narrow_launcher(int n);
 const void *thread_kernel_symbol(int n);
 const void *lanes_kernel_symbol(int n, int lanes, int layout);
 /* Segment widths compiled for size n (ascending), returns the count. */

@@ -1,5 +1,6 @@
-/* Lanes-per-system batched solve for the interleaved (SoA) layout, with the
- * global traffic staged through LDS (Section 3: coalesced accesses to the
+/* Lanes-per-system batched solve with tile-local pivoting for the interleaved
+ * (SoA) layout (strict and FMA solves with textbook pivoting: the same staging
+ * in kernels_seg_soa.h), with the global traffic staged through LDS (Section 3: coalesced accesses to the
  * batch; Section 3.2: several rows per thread, several systems per wave).
  *
  * The solve itself is the one of k_lanes (T lanes per system, K = ceil(n/T)
@@ -69,7 +70,7 @@ __device__ __forceinline__ int soa_sw(int i)
     return ((i >> Sh::SH) << Sh::LOG_SPH) & (Sh::S - 1);
 }
 
-template <int N, int T, bool F, bool Tl>
+template <int N, int T>
 __global__ void __launch_bounds__((soa_shape<N, T>::NT))
     __attribute__((amdgpu_waves_per_eu(soa_shape<N, T>::MIN_WAVES_EU))) k_lanes_soa(SolveArgs a, int factors)
 {
@@ -198,7 +199,7 @@ __global__ void __launch_bounds__((soa_shape<N, T>::NT))
     int pv[KP];
     static_for<0, KP>(LUPP_SF(sc) { pv[decltype(sc)::value] = 0; });
     constexpr bool kSettle = lanes_settle<N, T>();
-    const int inf = lanes_getrf_solve<N, T, F, Tl, Sh::CH, kSettle>(m, x, pos, g * T, [&](int k, int val) {
+    const int inf = lanes_getrf_solve<N, T, false, true, Sh::CH, kSettle>(m, x, pos, g * T, [&](int k, int val) {
         const int c = k / T;
         static_for<0, KP>(LUPP_SF(sc) {
             constexpr int cc = decltype(sc)::value;
@@ -274,17 +275,8 @@ hipError_t launch_lanes_soa(const SolveArgs &a, bool factors, hipStream_t st)
 {
     using Sh = soa_shape<N, T>;
     const int64_t blocks = (a.batch + Sh::S - 1) / Sh::S;
-    /* arithmetic x pivoting instances: strict, FMA, strict + tile-local */
-    if (a.fma && a.tile > 0) return hipErrorNotSupported;
-    if (a.fma)
-        hipLaunchKernelGGL((k_lanes_soa<N, T, true, false>), dim3((unsigned)blocks), dim3(Sh::NT), 0,
-                           st, a, (int)factors);
-    else if (a.tile > 0)
-        hipLaunchKernelGGL((k_lanes_soa<N, T, false, true>), dim3((unsigned)blocks), dim3(Sh::NT), 0,
-                           st, a, (int)factors);
-    else
-        hipLaunchKernelGGL((k_lanes_soa<N, T, false, false>), dim3((unsigned)blocks), dim3(Sh::NT),
-                           0, st, a, (int)factors);
+    hipLaunchKernelGGL((k_lanes_soa<N, T>), dim3((unsigned)blocks), dim3(Sh::NT), 0, st, a,
+                       (int)factors);
     return hipGetLastError();
 }
 

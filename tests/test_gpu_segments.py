@@ -1,0 +1,121 @@
+"""GPU parity of the lanes solver's own branches against the oracle, bit for
+bit (signed zeros too): the dispatcher's half-width kernels (large solve-only
+and interleaved batches), divisions at and beyond the range in which they
+share a reciprocal, equal high words in the pivot search, zero and negative
+zero right-hand sides, zero pivots in the first and second step of a pair."""
+import numpy as np
+import pytest
+
+import oracle
+from test_gpu_lupp import gpu_solve, variants
+from workloads import systems
+
+pytestmark = pytest.mark.gpu
+
+SMALL_BATCH = 32768  # the dispatcher's small-batch entries end here
+
+
+@pytest.fixture(scope="module")
+def L():
+    import paper_2609_15217_amd.lupp as L
+    return L
+
+
+@pytest.fixture(scope="module")
+def ctx(L):
+    return L.Context(0)
+
+
+def bits(a):
+    return np.ascontiguousarray(a, dtype=np.float64).view(np.int64)
+
+
+def assert_bits(ref, LU, x, pv, io, b, A=None):
+    assert np.array_equal(io, ref["info"])
+    assert np.array_equal(pv, ref["ipiv"])
+    assert np.array_equal(bits(LU), bits(ref["LU"] if A is None else A))
+    ok = ref["info"] == 0
+    assert np.array_equal(bits(x[ok]), bits(ref["x"][ok]))
+    assert np.array_equal(bits(x[~ok]), bits(b[~ok]))
+
+
+def edge_systems(n, seed):
+    """Well-scaled systems and the values the solver's fast paths exclude."""
+    A, b, _ = systems(n, 24, seed=seed)
+    out = [(A, b)]
+    # pivots, multipliers' numerators and solutions around 2^-400, 2^400 and
+    # 2^+-300, in the subnormal range, and graded rows or columns
+    for ea, eb in ((399, 399), (401, 401), (-399, -399), (-401, -401), (300, 0), (0, 305),
+                   (0, -305), (-600, -600), (600, 600), (-1040, -1040), (-1060, -1060), (200, -200)):
+        out.append((np.ldexp(A[:4], ea), np.ldexp(b[:4], eb)))
+    g = np.ldexp(A[:4], -450 * (np.arange(n) % 3)[None, None, :])  # rows 2^-450, 2^-900 apart
+    out.append((g, b[:4]))
+    c = np.ldexp(A[:4], -410 * (np.arange(n) % 2)[None, :, None])  # columns
+    out.append((c, b[:4]))
+    # right-hand sides with zeros and negative zeros, and matrices with them
+    z = b[:6].copy()
+    z[0] = 0.0
+    z[1] = -0.0
+    z[2, ::2] = 0.0
+    z[3, 1::2] = -0.0
+    out.append((A[:6], z))
+    T = np.stack([np.triu(A[0]), np.tril(A[1]), np.eye(n), -np.eye(n)])
+    T[T == 0] = 0.0
+    M = T.copy()
+    M[M == 0] = -0.0
+    out += [(T, b[:4]), (M, z[:4])]
+    # equal high words: low words decide; equal magnitudes: the position does
+    e = np.ones((4, n, n)) + np.ldexp(np.round(A[:4] * 64), -50)
+    out.append((e, b[:4]))
+    out.append((np.where(A[:4] > 0, 1.0, -1.0), b[:4]))
+    # zero pivots at the first, second and last steps, alone and together
+    for cols in ([0], [1], [0, 1], [n - 1], [n // 2], list(range(n))):
+        s = A[:2].copy()
+        s[:, [k for k in cols if k < n]] = 0.0
+        s[1] = np.where(s[1] == 0, -0.0, s[1])
+        out.append((s, z[:2]))
+    return np.concatenate([o[0] for o in out]), np.concatenate([o[1] for o in out])
+
+
+@pytest.mark.parametrize("n", [2, 3, 5, 8, 9, 12, 13, 16, 17, 24, 25, 32])
+def test_values_at_the_edges_of_the_fast_paths(L, ctx, n):
+    A, b = edge_systems(n, seed=7500 + n)
+    for fma in (False, True):
+        ref = oracle.gesv_batch_mode(A, b, fma=fma, threads=4)
+        for variant, lanes in variants(n):
+            if variant != 2:
+                continue
+            for layout in (L.LUPP_AOS, L.LUPP_SOA):
+                got = gpu_solve(L, ctx, A, b, layout, variant, lanes, fma=fma)
+                assert got[4]
+                assert_bits(ref, *got[:4], b)
+
+
+@pytest.mark.parametrize("n", list(range(9, 13)) + list(range(17, 25)))
+def test_half_width_kernels(L, ctx, n):
+    """Reached by the dispatcher alone, from 32768 systems on; the edge
+    systems are spread over the batch, whose last wave is not full."""
+    batch = SMALL_BATCH + 13
+    A, b, _ = systems(n, batch, seed=7600 + n)
+    E, eb = edge_systems(n, seed=7700 + n)
+    at = np.linspace(0, batch - 1, len(E)).astype(int)
+    A[at], b[at] = E, eb
+    for fma in (False, True):
+        ref = oracle.gesv_batch_mode(A, b, fma=fma, threads=8)
+        for layout in (L.LUPP_AOS, L.LUPP_SOA):
+            got = gpu_solve(L, ctx, A, b, layout, keep_a=True, fma=fma, lda=n + 1, stride_pad=3)
+            assert got[4]
+            assert_bits(ref, *got[:4], b, A=A)
+        got = gpu_solve(L, ctx, A, b, L.LUPP_SOA, fma=fma)
+        assert_bits(ref, *got[:4], b)
+
+
+def test_caller_chosen_entries_hold(L):
+    """An entry the caller set serves solve-only calls too."""
+    ctx = L.Context(0)
+    n, batch = 20, SMALL_BATCH
+    assert L.lupp_set_dispatch(ctx, n, L.LUPP_AOS, batch, L.LUPP_VARIANT_LANES, 32, 2) == 0
+    assert L.lupp_get_dispatch(ctx, n, L.LUPP_AOS, batch) == (L.LUPP_VARIANT_LANES, 32, 2)
+    A, b, _ = systems(n, batch, seed=7800)
+    ref = oracle.gesv_batch(A, b, threads=8)
+    assert_bits(ref, *gpu_solve(L, ctx, A, b, L.LUPP_AOS, keep_a=True)[:4], b, A=A)
