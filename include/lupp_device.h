@@ -131,43 +131,62 @@ __device__ __forceinline__ int pivot_tile_end(int k, int n, int tile)
     return e < n ? e : n;
 }
 
-/* Pivot of column k over rows k .. N-1 (element (i, k) at a[k][i]): the
- * largest magnitude, the lowest row among equal ones, by a pairwise (tree)
- * reduction in which the right (higher) half wins only when strictly larger:
- * the choice of a left-to-right scan for any non-NaN column, with
- * ceil(log2(N - k)) dependent compare/select levels instead of N - k - 1.
- * best, pv, p: magnitude, signed value and row of the pivot. */
+/* max(|x|, |y|) in one instruction (a NaN operand loses to a number) */
+__device__ __forceinline__ double max_abs(double x, double y)
+{
+    double r;
+    asm("v_max_f64 %0, |%1|, |%2|" : "=v"(r) : "v"(x), "v"(y));
+    return r;
+}
+
+/* Largest magnitude of column k over rows k .. N-1 (element (i, k) at
+ * a[k][i]), as a tree: ceil(log2(N - k)) dependent instructions. */
 template <int N, int k>
-__device__ __forceinline__ void thread_pivot_tree(const double (&a)[N][N], double &best, double &pv,
-                                                  int &p)
+__device__ __forceinline__ double thread_pivot_max(const double (&a)[N][N])
 {
     constexpr int M = N - k;
-    double mg[M], vl[M];
-    int id[M];
-    static_for<0, M>(LUPP_SF(ic) {
-        constexpr int i = decltype(ic)::value;
-        mg[i] = fabs(a[k][k + i]);
-        vl[i] = a[k][k + i];
-        id[i] = k + i;
-    });
+    if constexpr (M == 1) return fabs(a[k][k]);
+    double mg[M];
+    static_for<0, M>(LUPP_SF(ic) { mg[decltype(ic)::value] = a[k][k + decltype(ic)::value]; });
     static_for<0, 6>(LUPP_SF(lc) {
         constexpr int st = 1 << decltype(lc)::value;
-        if constexpr (st < M) {
-            static_for<0, (M + 2 * st - 1) / (2 * st)>(LUPP_SF(pc) {
-                constexpr int i = decltype(pc)::value * 2 * st;
-                if constexpr (i + st < M) {
-                    const bool gt = mg[i + st] > mg[i];
-                    mg[i] = gt ? mg[i + st] : mg[i];
-                    vl[i] = gt ? vl[i + st] : vl[i];
-                    id[i] = gt ? id[i + st] : id[i];
-                }
-            });
-        }
+        static_for<0, (M + 2 * st - 1) / (2 * st)>(LUPP_SF(pc) {
+            constexpr int i = decltype(pc)::value * 2 * st;
+            if constexpr (i + st < M) mg[i] = max_abs(mg[i], mg[i + st]);
+        });
     });
-    best = mg[0];
-    pv = vl[0];
-    p = id[0];
+    return mg[0];
 }
+
+/* Exchange xi and yi in the lanes of m, a subset of the active lanes: three
+ * 64-bit moves per pair under that mask (12.6 cycles on gfx950) where selects
+ * take four 32-bit ones (17.6) and v_swap_b32 two of 8.2. */
+#define LUPP_SWAP_IN "s_mov_b64 %[e], exec\n\ts_mov_b64 exec, %[m]\n\t"
+#define LUPP_SWAP_OUT "s_mov_b64 exec, %[e]"
+#define LUPP_SWAP(i)                                                                         \
+    "v_mov_b64 %[t], %[x" #i "]\n\tv_mov_b64 %[x" #i "], %[y" #i "]\n\tv_mov_b64 %[y" #i \
+    "], %[t]\n\t"
+__device__ __forceinline__ void masked_swap(uint64_t m, double &x0, double &y0)
+{
+    double t;
+    uint64_t e;
+    asm(LUPP_SWAP_IN LUPP_SWAP(0) LUPP_SWAP_OUT
+        : [x0] "+v"(x0), [y0] "+v"(y0), [t] "=&v"(t), [e] "=&s"(e) : [m] "s"(m));
+}
+__device__ __forceinline__ void masked_swap(uint64_t m, double &x0, double &y0, double &x1,
+                                            double &y1, double &x2, double &y2, double &x3,
+                                            double &y3)
+{
+    double t;
+    uint64_t e;
+    asm(LUPP_SWAP_IN LUPP_SWAP(0) LUPP_SWAP(1) LUPP_SWAP(2) LUPP_SWAP(3) LUPP_SWAP_OUT
+        : [x0] "+v"(x0), [y0] "+v"(y0), [x1] "+v"(x1), [y1] "+v"(y1), [x2] "+v"(x2), [y2] "+v"(y2),
+          [x3] "+v"(x3), [y3] "+v"(y3), [t] "=&v"(t), [e] "=&s"(e)
+        : [m] "s"(m));
+}
+#undef LUPP_SWAP
+#undef LUPP_SWAP_IN
+#undef LUPP_SWAP_OUT
 
 /* Pivoting rule (all solvers): textbook partial pivoting unless the kTile
  * parameter is set (then tile >= 1 is required): tile-local pivoting, where
@@ -176,23 +195,24 @@ __device__ __forceinline__ void thread_pivot_tree(const double (&a)[N][N], doubl
  * k .. n-1 searched; ties go to the lowest row (position) either way.
  * Without kTile the solvers contain no tile code at all.
  *
- * Search shape (thread solver): a running left-to-right scan where the
- * factors are kept (fewer values live: n = 8 stays free of scratch at three
- * waves per SIMD), a pairwise tree for solve-only calls such as the Newton
- * steps (a dependent chain of ceil(log2(n - k)) compare/selects instead of
- * n - k - 1). Both pick the same row unless the column holds a NaN.
+ * Search (thread solver): the largest magnitude M of the column by a tree of
+ * v_max_f64, then, row by row, the lanes whose entry has magnitude M and which
+ * no earlier row has served: two instructions per candidate where carrying the
+ * value and row of a running best takes seven, and the lowest such row is
+ * textbook pivoting's choice (for a column without NaN). The tile-local rule,
+ * with its bounded first search, carries the running best.
  *
- * Interchange: the pivot row p is data while register indices are not, so
- * rows k and p are swapped by selects, one candidate row i at a time, and
- * the swap with row i runs only if some lane of the wave chose it (a
- * wave-uniform branch on a ballot). A wave whose systems pivot alike - the
- * Jacobians of one law at neighbouring points, which nearly always pivot on
- * row k or the flow-rule row - skips most of the selects; for unrelated
- * random systems every row is some lane's pivot, and the branches still
- * bound how far the compiler interleaves the swaps: measured on gfx950 this
- * form needs far fewer registers than selecting the pivot row out of all
- * candidates column by column (n = 8: 170 VGPRs against 256 plus scratch;
- * n = 13: no scratch against 1204 bytes per lane).
+ * Interchange: the pivot row is data while register indices are not, so rows
+ * k and i are exchanged in the lanes that chose i, for one candidate row i at
+ * a time, and only if some lane of the wave chose it (a wave-uniform branch).
+ * A wave whose systems pivot alike - the Jacobians of one law at neighbouring
+ * points, which nearly always pivot on row k or the flow-rule row - skips
+ * most of the exchanges; the branches also bound how far the compiler
+ * interleaves them (selecting the pivot row out of all candidates column by
+ * column needed 256 VGPRs and scratch at n = 8).
+ * Measured with selects and the running best before (fused Newton updates,
+ * 2^20 points of 7 unknowns / 2^19 points of 13 / 200003 points of 13 with
+ * the tangent): 602 / 1444 / 974 us -> 522 / 1389 / 892 us.
  *
  * kRecip (solve only, kFactors false): one division per step - the pivot's
  * reciprocal - by which the multipliers are formed and, stored in the
@@ -208,72 +228,94 @@ __device__ __forceinline__ int thread_getrf_solve(double (&a)[N][N], double (&b)
     int info = 0;
     static_for<0, N>(LUPP_SF(kc) {
         constexpr int k = decltype(kc)::value;
-        /* pivot search over rows k .. k1-1 of column k, then, if needed, over
-         * every row k .. N-1 */
-        const int k1 = kTile ? pivot_tile_end(k, N, tile) : N;
-        double best = fabs(a[k][k]);
-        double pv = a[k][k];
-        int p = k;
-        if constexpr (!kTile && !kFactors) {
-            thread_pivot_tree<N, k>(a, best, pv, p);
+        double pv, rp = 0.0;
+        bool zero;
+        if constexpr (!kTile) {
+            const double best = thread_pivot_max<N, k>(a);
+            /* kRecip: the reciprocal needs only the magnitude, so its latency
+             * runs under the interchange (a zero pivot gives an unused infinity) */
+            if constexpr (kRecip) rp = 1.0 / best;
+            zero = best == 0.0;
+            info = (zero && info == 0) ? k + 1 : info;
+            /* solve-only calls on systems that spill into AGPRs (the 13 x 13
+             * Newton steps): fenced, see settle */
+            if constexpr (!kFactors && N >= 10) settle(info);
+            int p = k;
+            uint64_t open = ~__ballot(fabs(a[k][k]) == best);
+            static_for<k + 1, N>(LUPP_SF(ic) {
+                constexpr int i = decltype(ic)::value;
+                const uint64_t hit = __ballot(fabs(a[k][i]) == best) & open;
+                open &= ~hit;
+                if (hit != 0) {
+                    constexpr int j0 = kFactors ? 0 : k, j4 = j0 + (N - j0) / 4 * 4;
+                    static_for<0, (N - j0) / 4>(LUPP_SF(qc) {
+                        constexpr int j = j0 + 4 * decltype(qc)::value;
+                        masked_swap(hit, a[j][k], a[j][i], a[j + 1][k], a[j + 1][i], a[j + 2][k],
+                                    a[j + 2][i], a[j + 3][k], a[j + 3][i]);
+                    });
+                    static_for<j4, N>(LUPP_SF(jc) {
+                        constexpr int j = decltype(jc)::value;
+                        masked_swap(hit, a[j][k], a[j][i]);
+                    });
+                    masked_swap(hit, b[k], b[i]);
+                    p = __builtin_amdgcn_inverse_ballot_w64(hit) ? i : p;
+                }
+            });
+            ipiv[k] = p + 1;
+            pv = a[k][k];
+            if constexpr (kRecip) rp = __builtin_copysign(rp, pv);
         } else {
+            /* the rows k .. k1-1 first, then, if needed, every row k .. N-1 */
+            const int k1 = pivot_tile_end(k, N, tile);
+            double best = fabs(a[k][k]);
+            pv = a[k][k];
+            int p = k;
             static_for<k + 1, N>(LUPP_SF(ic) {
                 constexpr int i = decltype(ic)::value;
                 const double v = fabs(a[k][i]);
-                bool gt = v > best;
-                if constexpr (kTile) gt = gt & (i < k1);
+                const bool gt = (v > best) & (i < k1);
                 best = gt ? v : best;
                 pv = gt ? a[k][i] : pv;
                 p = gt ? i : p;
             });
-        }
-        if (kTile && __ballot(best < thresh) != 0) {
-            const bool wide = best < thresh;
-            double bw = fabs(a[k][k]);
-            double pw = a[k][k];
-            int qw = k;
+            if (__ballot(best < thresh) != 0) {
+                const bool wide = best < thresh;
+                double bw = fabs(a[k][k]);
+                double pw = a[k][k];
+                int qw = k;
+                static_for<k + 1, N>(LUPP_SF(ic) {
+                    constexpr int i = decltype(ic)::value;
+                    const double v = fabs(a[k][i]);
+                    const bool gt = v > bw;
+                    bw = gt ? v : bw;
+                    pw = gt ? a[k][i] : pw;
+                    qw = gt ? i : qw;
+                });
+                best = wide ? bw : best;
+                pv = wide ? pw : pv;
+                p = wide ? qw : p;
+            }
+            ipiv[k] = p + 1;
+            zero = (pv == 0.0);
+            info = (zero && info == 0) ? k + 1 : info;
+            /* exactly one candidate i matches p in a lane, so the conditional
+             * swaps compose to the single interchange */
             static_for<k + 1, N>(LUPP_SF(ic) {
                 constexpr int i = decltype(ic)::value;
-                const double v = fabs(a[k][i]);
-                const bool gt = v > bw;
-                bw = gt ? v : bw;
-                pw = gt ? a[k][i] : pw;
-                qw = gt ? i : qw;
+                const bool hit = (p == i);
+                if (__ballot(hit) != 0) {
+                    static_for<(kFactors ? 0 : k), N>(LUPP_SF(jc) {
+                        constexpr int j = decltype(jc)::value;
+                        const double rk = a[j][k], ri = a[j][i];
+                        a[j][k] = hit ? ri : rk;
+                        a[j][i] = hit ? rk : ri;
+                    });
+                    const double bk = b[k], bi = b[i];
+                    b[k] = hit ? bi : bk;
+                    b[i] = hit ? bk : bi;
+                }
             });
-            best = wide ? bw : best;
-            pv = wide ? pw : pv;
-            p = wide ? qw : p;
         }
-        ipiv[k] = p + 1;
-        const bool zero = (pv == 0.0);
-        info = (zero && info == 0) ? k + 1 : info;
-        /* solve-only calls on systems that spill into AGPRs (the 13 x 13
-         * Newton steps): fenced, see settle - 190 -> 146 AGPRs, no VGPR
-         * spill, 2991 -> 2891 us; at 7 x 7 it removes registers without
-         * adding a wave (641 vs 632 us) */
-        if constexpr (!kFactors && N >= 10) settle(info);
-        /* kRecip: the reciprocal needs only the pivot value, so its latency
-         * runs under the interchange below (a zero pivot gives an unused
-         * infinity) */
-        const double rp = kRecip ? 1.0 / pv : 0.0;
-
-        /* interchange rows k and p: exactly one candidate i matches p in a
-         * lane, so the conditional swaps compose to the single interchange */
-        static_for<k + 1, N>(LUPP_SF(ic) {
-            constexpr int i = decltype(ic)::value;
-            const bool hit = (p == i);
-            if (__ballot(hit) != 0) {
-                static_for<(kFactors ? 0 : k), N>(LUPP_SF(jc) {
-                    constexpr int j = decltype(jc)::value;
-                    const double rk = a[j][k], ri = a[j][i];
-                    a[j][k] = hit ? ri : rk;
-                    a[j][i] = hit ? rk : ri;
-                });
-                const double bk = b[k], bi = b[i];
-                b[k] = hit ? bi : bk;
-                b[i] = hit ? bk : bi;
-            }
-        });
 
         if (!zero) {
             /* multipliers, Schur-complement update, forward substitution */
