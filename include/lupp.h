@@ -130,7 +130,7 @@ int lupp_check_solve_args(int n, int64_t batch, int layout, const double *A, int
  * (histogram, plan, scatter; workspace owned by the context, grown with
  * hipMalloc when a larger batch arrives) and serves the sizes from one
  * kernel launch per size class queued back to back on `stream` (sizes
- * 24..32, 17..23, then 1..16: each kernel's register budget fits its sizes),
+ * 22..32, 17..21, then 1..16: each kernel's register budget fits its sizes),
  * largest sizes first; no host synchronisation. Each size uses the lane count of the
  * context's ragged table (lupp_set_ragged_lanes). A system whose n is
  * outside 1..32 gets info = -1 and is not touched. flags: LUPP_KEEP_A,
@@ -149,8 +149,8 @@ int lupp_batched_solve_ragged(lupp_ctx *ctx, int64_t batch, const int32_t *n,
  * size-aware dispatch): group g holds groups[g].batch systems of size
  * groups[g].n, AoS, system s at A + s*strideA (column-major, leading
  * dimension lda), right-hand side at b + s*strideB, pivots at ipiv + s*n and
- * info[s]. The groups are served by one launch per size class (sizes 17..32,
- * then 1..16), kMaxGroups = 32 groups per launch, largest sizes first, each
+ * info[s]. The groups are served by one launch per size class (sizes 22..32,
+ * 17..21, then 1..16), kMaxGroups = 32 groups per launch, largest sizes first, each
  * size with the lane count of the context's ragged table; every workgroup
  * takes one work item of one group, found in the launch's argument table.
  * No device workspace, no grouping kernels, no host synchronisation; the
@@ -246,7 +246,11 @@ int lupp_force_variant(lupp_ctx *ctx, int variant, int lanes, int wpb);
 
 /* Set / read the dispatch-table entry used for size n, layout and batches of
  * the size class of `batch` (below 32768 systems, or from 32768 on). The
- * table starts from the entries the autotuner measured on gfx950. */
+ * table starts from the entries the autotuner measured on gfx950 with the
+ * factors written. Until the caller sets or autotunes an entry, batches from
+ * 32768 systems on may run a kernel that measured faster without the factors
+ * (LUPP_KEEP_A) or in the interleaved layout, among them widths that cannot be
+ * forced; results do not depend on it. */
 int lupp_set_dispatch(lupp_ctx *ctx, int n, int layout, int64_t batch, int variant, int lanes,
                       int wpb);
 int lupp_get_dispatch(lupp_ctx *ctx, int n, int layout, int64_t batch, int *variant, int *lanes,

@@ -328,16 +328,18 @@ __device__ __forceinline__ int seg_getrf_solve(double (&a)[(N + T - 1) / T][N],
         });
         odd |= bad;
         double y = reciprocal(pv), q[K], e[K];
-        static_for<0, K>(LUPP_SF(sc) {
-            constexpr int s = decltype(sc)::value;
-            masked_mov(hit[s], ry[s], y);
-            q[s] = a[s][k] * y;
-            e[s] = __builtin_fma(-pv, q[s], a[s][k]);
-        });
-        if (__builtin_expect(bad != 0, 0)) {
+        static_for<0, K>(LUPP_SF(sc) { masked_mov(hit[decltype(sc)::value], ry[decltype(sc)::value], y); });
+        if (__builtin_expect(bad == 0, 1)) {
+            static_for<0, K>(LUPP_SF(sc) {
+                constexpr int s = decltype(sc)::value;
+                q[s] = a[s][k] * y;
+                e[s] = __builtin_fma(-pv, q[s], a[s][k]);
+            });
+        } else {
             static_for<0, K>(LUPP_SF(sc) {
                 constexpr int s = decltype(sc)::value;
                 q[s] = a[s][k] / pv;
+                settle(q[s]); /* one division at a time */
                 e[s] = __builtin_copysign(0.0, q[s]); /* fma(e, 1, q) == q, signed zeros too */
             });
             y = 1.0;

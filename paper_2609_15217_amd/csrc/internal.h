@@ -103,9 +103,9 @@ bool tuned_ragged(int n, int *lanes);
 constexpr int kRaggedSmallMax = 16;
 
 /* Lane counts compiled into the ragged kernels for size n. Sizes up to 16
- * share one kernel held to 3 waves per SIMD: the thread path up to n = 5 and
+ * share one kernel at 4 waves per SIMD: the thread path up to n = 5 and
  * segments of 2, 4, 8 or 16 lanes where the rows fit; sizes 17..32 run in two
- * kernels (17..23 at 3 waves per SIMD, 24..32 at 2) with 16 lanes, two rows
+ * kernels (17..21 at 4 waves per SIMD, 22..32 at 3) with 16 lanes, two rows
  * each (one row on each of 32 lanes measured slower at every one of these
  * sizes, standalone and in the ragged kernel, so it is not compiled in: it
  * would double the kernels' code). */

@@ -6,9 +6,8 @@
  * into work items of one workgroup round, and a scatter of system indices
  * into the bins. The solve is then one launch per size class - classes of
  * sizes with the same register budget, so that each class runs at the
- * occupancy its largest size allows - whose workgroups walk the class's work
- * items with a grid stride (no work counter: the plan gives every workgroup
- * its items), or one launch per size.
+ * occupancy its largest size allows - with one workgroup per work item (the
+ * plan gives every workgroup its item), or one launch per size.
  *
  * System s: matrix column-major at A + offA[s] (lda = n[s]), right-hand side
  * and pivots at offset offB[s], info[s].
@@ -19,21 +18,23 @@
 #include <utility>
 
 #include "internal.h"
-#include "lupp_device.h"
+#include "kernels_seg.h"
+#include "lupp_segments.h"
 
 namespace lupp {
 
 constexpr int kRaggedWaves = 4;       /* wave64s per workgroup */
 constexpr int kRaggedThreads = 64 * kRaggedWaves;
 
-/* Size classes of the ragged and grouped kernels, largest sizes first:
- * 24..32 (16-lane segments, up to 217 VGPRs: 2 waves per SIMD), 17..23
- * (16-lane segments, 164 VGPRs: 3 waves; with n = 24 in it the class kernel
- * spilled) and 1..16. */
+/* Size classes of the ragged and grouped kernels, largest sizes first, each
+ * the sizes with one register budget of the 16-lane solver (seg_shape): 22..32
+ * (168 VGPRs, 3 waves per SIMD), 17..21 (128, 4 waves) and 1..16 (128). */
 constexpr int kRaggedClasses = 3;
-__host__ __device__ constexpr int ragged_class_lo(int c) { return c == 0 ? 24 : (c == 1 ? 17 : 1); }
-__host__ __device__ constexpr int ragged_class_hi(int c) { return c == 0 ? 32 : (c == 1 ? 23 : 16); }
-__host__ __device__ constexpr int ragged_class_of(int n) { return n >= 24 ? 0 : (n >= 17 ? 1 : 2); }
+__host__ __device__ constexpr int ragged_class_lo(int c) { return c == 0 ? 22 : (c == 1 ? 17 : 1); }
+__host__ __device__ constexpr int ragged_class_hi(int c) { return c == 0 ? 32 : (c == 1 ? 21 : 16); }
+__host__ __device__ constexpr int ragged_class_of(int n) { return n >= 22 ? 0 : (n >= 17 ? 1 : 2); }
+/* waves per SIMD each class kernel is compiled for */
+__host__ __device__ constexpr int ragged_class_waves(int c) { return c == 0 ? 3 : 4; }
 
 struct RaggedPlan {
     int32_t count[33];      /* systems of each size */
@@ -54,6 +55,7 @@ struct RaggedArgs {
     int factors;
     int32_t *sorted;
     RaggedPlan *plan;
+    int32_t item0; /* first work item of this launch within its class */
     /* lanes per system for each size (ragged_lanes_ok). Words, not bytes:
      * 4-byte-aligned kernel arguments are read by scalar loads, where a byte
      * array is loaded into vector registers (and, in the looping
@@ -70,6 +72,24 @@ __host__ __device__ constexpr int ragged_per_round(int T)
 }
 
 __host__ __device__ constexpr int ragged_per_item(int T) { return ragged_per_round(T); }
+
+/* LDS doubles of a workgroup: the solver records of its segments, for the
+ * size and lane count of LO..HI that takes most */
+template <int LO, int HI>
+__host__ __device__ constexpr int ragged_lds()
+{
+    int most = 2;
+    if constexpr (LO <= HI) {
+        for (int T = 2; T <= 16; T *= 2)
+            if (ragged_lanes_ok(LO, T)) {
+                const int d = ragged_per_round(T) * seg_lds<LO>::kStride;
+                most = d > most ? d : most;
+            }
+        const int rest = ragged_lds<LO + 1, HI>();
+        most = rest > most ? rest : most;
+    }
+    return most;
+}
 
 /* Where the j-th system of a work item lives: matrix (column-major, leading
  * dimension lda()), right-hand side, pivots and info. */
@@ -92,11 +112,21 @@ struct RaggedLoc {
     __device__ __forceinline__ int64_t lda() const { return N; }
 };
 
+/* The lane number, computed where it stands: kept out of the registers that
+ * live across the work-item loop and the solves. */
+__device__ __forceinline__ int fresh_lane()
+{
+    int l;
+    asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(l));
+    return l;
+}
+
 /* Solve the cnt (>= 1) systems of one work item with the whole workgroup, T
  * lanes per system (T == 1: one thread per system). Threads or segments
- * without a system point at system 0, load zeros and store nothing. */
-template <int N, int T, typename Loc>
-__device__ __forceinline__ void solve_item(const Loc &loc, int cnt, int factors)
+ * without a system point at system 0, load zeros and store nothing. lds: the
+ * workgroup's solver records (ragged_lds); W: waves per SIMD of the kernel. */
+template <int N, int T, int W, typename Loc>
+__device__ __forceinline__ void solve_item(const Loc &loc, int cnt, int factors, double *lds)
 {
     const int64_t lda = loc.lda();
     if constexpr (T == 1) {
@@ -133,82 +163,85 @@ __device__ __forceinline__ void solve_item(const Loc &loc, int cnt, int factors)
         }
     } else {
         constexpr int K = lanes_shape<N, T>::K;
+        constexpr bool PF = seg_shape<N, T>::waves(seg_shape<N, T>::kNeed + 28) >= W;
         constexpr int SPW = 64 / T;
-        const int lane = (int)__lane_id();
-        const int g = lane / T, t = lane % T;
-        const int wave = threadIdx.x >> 6;
-        const int j0 = wave * SPW + g;
-        const bool act = j0 < cnt;
-        const SysPtrs p = loc.sys(act ? j0 : 0); /* cnt >= 1: system 0 exists */
+        const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+        /* rebuilt after the solve, with the system's pointers, so that neither
+         * stays live across it */
+        int g, t;
+        bool act;
+        auto set_geometry = [&]() __attribute__((always_inline)) {
+            const int lane = fresh_lane();
+            g = lane / T;
+            t = lane % T;
+            act = wave * SPW + g < cnt;
+        };
+        set_geometry();
         double m[K][N], x[K];
         int pos[K];
-        static_for<0, K>([&](auto sc) __attribute__((always_inline)) {
-            constexpr int sl = decltype(sc)::value;
-            const int r = t + sl * T;
-            const bool ok = act && r < N;
-            pos[sl] = r < N ? r : -1;
-            static_for<0, N>([&](auto jc) __attribute__((always_inline)) {
-                constexpr int j = decltype(jc)::value;
-                m[sl][j] = ok ? p.A[r + j * lda] : 0.0;
-            });
-            x[sl] = ok ? p.b[r] : 0.0;
-        });
-        constexpr int KP = (N + T - 1) / T;
-        int pv[KP];
-        static_for<0, KP>([&](auto sc) __attribute__((always_inline)) { pv[decltype(sc)::value] = 0; });
-        /* 16-column pivot-row broadcasts where 16-lane segments already need
-         * more than 168 VGPRs (n >= 26), as in the SoA kernels */
-        constexpr int CH = (T == 16 && N >= 26) ? 16 : 8;
-        const int inf = lanes_getrf_solve<N, T, false, false, CH>(m, x, pos, g * T, [&](int k, int v) {
-            const int c = k / T;
-            static_for<0, KP>([&](auto sc) __attribute__((always_inline)) {
-                constexpr int cc = decltype(sc)::value;
-                if (cc == c) pv[cc] = (t == k % T) ? v : pv[cc];
-            });
-        });
-        if (act) {
+        {
+            const SysPtrs p = loc.sys(act ? wave * SPW + g : 0); /* cnt >= 1: system 0 exists */
             static_for<0, K>([&](auto sc) __attribute__((always_inline)) {
                 constexpr int sl = decltype(sc)::value;
-                if (pos[sl] >= 0) {
-                    if (factors) {
-                        static_for<0, N>([&](auto jc) __attribute__((always_inline)) {
-                            constexpr int j = decltype(jc)::value;
-                            p.A[pos[sl] + j * lda] = m[sl][j];
-                        });
-                    }
-                    if (inf == 0) p.b[pos[sl]] = x[sl];
-                }
+                const int r = t + sl * T;
+                const bool ok = act && r < N;
+                pos[sl] = r < N ? r : -1;
+                static_for<0, N>([&](auto jc) __attribute__((always_inline)) {
+                    constexpr int j = decltype(jc)::value;
+                    m[sl][j] = ok ? p.A[r + j * lda] : 0.0;
+                });
+                x[sl] = ok ? p.b[r] : 0.0;
             });
-            static_for<0, KP>([&](auto sc) __attribute__((always_inline)) {
-                constexpr int c = decltype(sc)::value;
-                if (t + c * T < N) p.ipiv[t + c * T] = pv[c];
+        }
+        double *rec = lds + (wave * SPW + g) * seg_lds<N>::kStride;
+        const int inf = seg_getrf_solve<N, T, false, seg_shape<N, T>::CH, PF>(m, x, pos, rec);
+        set_geometry();
+        rec = lds + (wave * SPW + g) * seg_lds<N>::kStride;
+        if (act) {
+            const SysPtrs p = loc.sys(wave * SPW + g);
+            const int *seq = reinterpret_cast<const int *>(rec + seg_lds<N>::kPos);
+            static_for<0, K>([&](auto sc) __attribute__((always_inline)) {
+                constexpr int sl = decltype(sc)::value;
+                if (factors && pos[sl] >= 0) {
+                    static_for<0, N>([&](auto jc) __attribute__((always_inline)) {
+                        constexpr int j = decltype(jc)::value;
+                        p.A[pos[sl] + j * lda] = m[sl][j];
+                    });
+                }
+                const int r = t + sl * T;
+                if (r < N) {
+                    if (inf == 0) p.b[r] = rec[r];
+                    p.ipiv[r] = seq[r] + 1;
+                }
             });
             if (t == 0) *p.info = inf;
         }
     }
 }
 
-template <int N, int T>
-__device__ __forceinline__ void ragged_item(const RaggedArgs &a, int first, int cnt)
+template <int N, int T, int W>
+__device__ __forceinline__ void ragged_item(const RaggedArgs &a, int first, int cnt, double *lds)
 {
-    const RaggedLoc<N> loc{a, a.sorted + a.plan->bin_start[N] + first};
-    solve_item<N, T>(loc, cnt, a.factors);
+    /* uniform: in scalar registers across the solve */
+    const int at = __builtin_amdgcn_readfirstlane(a.plan->bin_start[N] + first);
+    const RaggedLoc<N> loc{a, opaque_ptr(a.sorted + at)};
+    solve_item<N, T, W>(loc, cnt, a.factors, lds);
 }
 
-template <int N, int T>
-__device__ __forceinline__ void ragged_run_item_t(const RaggedArgs &a, int it)
+template <int N, int T, int W>
+__device__ __forceinline__ void ragged_run_item_t(const RaggedArgs &a, int it, double *lds)
 {
-    const int first = (it - a.plan->item_start[N]) * ragged_per_item(T);
-    const int rest = a.plan->count[N] - first;
-    if (rest > 0) ragged_item<N, T>(a, first, rest < ragged_per_item(T) ? rest : ragged_per_item(T));
+    const int first = __builtin_amdgcn_readfirstlane((it - a.plan->item_start[N]) * ragged_per_item(T));
+    const int rest = __builtin_amdgcn_readfirstlane(a.plan->count[N] - first);
+    if (rest > 0) ragged_item<N, T, W>(a, first, rest < ragged_per_item(T) ? rest : ragged_per_item(T), lds);
 }
 
-template <int N, int T>
-__device__ __forceinline__ bool ragged_try_lanes(const RaggedArgs &a, int lanes, int it)
+template <int N, int T, int W>
+__device__ __forceinline__ bool ragged_try_lanes(const RaggedArgs &a, int lanes, int it, double *lds)
 {
     if constexpr (ragged_lanes_ok(N, T)) {
         if (lanes == T) {
-            ragged_run_item_t<N, T>(a, it);
+            ragged_run_item_t<N, T, W>(a, it, lds);
             return true;
         }
     }
@@ -217,63 +250,70 @@ __device__ __forceinline__ bool ragged_try_lanes(const RaggedArgs &a, int lanes,
 
 /* Solve the work item `it` of size N (all threads of the workgroup) with the
  * lane count the table gives for N (uniform across the workgroup). */
-template <int N>
-__device__ __forceinline__ void ragged_run_item(const RaggedArgs &a, int it)
+template <int N, int W>
+__device__ __forceinline__ void ragged_run_item(const RaggedArgs &a, int it, double *lds)
 {
     if constexpr (N > kRaggedSmallMax) {
         /* 16 lanes: the only count compiled for these sizes (ragged_lanes_ok) */
-        ragged_run_item_t<N, 16>(a, it);
+        ragged_run_item_t<N, 16, W>(a, it, lds);
     } else {
         const int lanes = __builtin_amdgcn_readfirstlane((int)a.lanes[N]);
-        (void)(ragged_try_lanes<N, 1>(a, lanes, it) || ragged_try_lanes<N, 2>(a, lanes, it) ||
-               ragged_try_lanes<N, 4>(a, lanes, it) || ragged_try_lanes<N, 8>(a, lanes, it) ||
-               ragged_try_lanes<N, 16>(a, lanes, it));
+        (void)(ragged_try_lanes<N, 1, W>(a, lanes, it, lds) || ragged_try_lanes<N, 2, W>(a, lanes, it, lds) ||
+               ragged_try_lanes<N, 4, W>(a, lanes, it, lds) || ragged_try_lanes<N, 8, W>(a, lanes, it, lds) ||
+               ragged_try_lanes<N, 16, W>(a, lanes, it, lds));
     }
 }
 
 /* One size per launch: workgroup b solves work item b of size N. */
 template <int N>
-__global__ void __launch_bounds__(kRaggedThreads) k_ragged_one(RaggedArgs a)
+__global__ void __launch_bounds__(kRaggedThreads)
+    __attribute__((amdgpu_waves_per_eu(ragged_class_waves(ragged_class_of(N))))) k_ragged_one(RaggedArgs a)
 {
+    __shared__ __align__(16) double lds[ragged_lds<N, N>()];
     const int it = a.plan->item_start[N] + (int)xcd_block(blockIdx.x, gridDim.x);
-    ragged_run_item<N>(a, it);
+    ragged_run_item<N, ragged_class_waves(ragged_class_of(N))>(a, it, lds);
 }
 
-template <int N>
-__device__ __forceinline__ bool ragged_try(const RaggedArgs &a, int n, int it)
+template <int N, int W>
+__device__ __forceinline__ bool ragged_try(const RaggedArgs &a, int n, int it, double *lds)
 {
     if (n != N) return false;
-    ragged_run_item<N>(a, it);
+    ragged_run_item<N, W>(a, it, lds);
     return true;
 }
 
-template <int LO, int... Ns>
-__device__ __forceinline__ void ragged_dispatch(const RaggedArgs &a, int n, int it,
+template <int LO, int W, int... Ns>
+__device__ __forceinline__ void ragged_dispatch(const RaggedArgs &a, int n, int it, double *lds,
                                                 std::integer_sequence<int, Ns...>)
 {
-    (void)(ragged_try<LO + Ns>(a, n, it) || ...);
+    (void)(ragged_try<LO + Ns, W>(a, n, it, lds) || ...);
 }
 
-/* The work items of class C (sizes LO..HI): workgroup w of a grid of G
- * takes items class_start[C] + w, + w + G, ... (w remapped so that the
- * workgroups of one XCD take neighbouring items). Items come largest size
- * first and every workgroup gets the same mix, so the grid finishes within
- * about one item of its mean. The size of an item is the smallest m whose
- * first item is at or before it (empty sizes start where the next one does). */
+/* Work item a.item0 + b of class C (sizes LO..HI) by workgroup b (remapped so
+ * that the workgroups of one XCD take neighbouring items; largest sizes first).
+ * The host does not know how many items a class has, so the grid is the bound
+ * that the batch size gives, and workgroups without an item end at once: 0.22 ns
+ * each (500000 empty workgroups: 109 us), about 1% of the mixed batch of 2
+ * million systems. Walking the items with a resident grid instead costs
+ * registers that the solver needs: 36 to 96 bytes per lane of scratch at these
+ * occupancies. The size of an item is the smallest m whose first item is at or
+ * before it (empty sizes start where the next one does). */
 template <int C>
-__device__ __forceinline__ void ragged_class_loop(const RaggedArgs &a)
+__device__ __forceinline__ void ragged_class_item(const RaggedArgs &a)
 {
     constexpr int LO = ragged_class_lo(C), HI = ragged_class_hi(C);
+    __shared__ __align__(16) double lds[ragged_lds<LO, HI>()];
     const RaggedPlan *plan = a.plan;
-    const int end = plan->class_start[C + 1];
-    const int G = (int)gridDim.x;
-    for (int it = plan->class_start[C] + (int)xcd_block(blockIdx.x, gridDim.x); it < end; it += G) {
-        int n = HI;
-        for (int m = HI - 1; m >= LO; --m)
-            if (plan->item_start[m] <= it) n = m;
-        n = __builtin_amdgcn_readfirstlane(n);
-        ragged_dispatch<LO>(a, n, it, std::make_integer_sequence<int, HI - LO + 1>{});
-    }
+    const int c0 = __builtin_amdgcn_readfirstlane(plan->class_start[C] + a.item0);
+    const int left = __builtin_amdgcn_readfirstlane(plan->class_start[C + 1] - c0);
+    const int G = left < (int)gridDim.x ? left : (int)gridDim.x;
+    if ((int)blockIdx.x >= G) return;
+    const int it = c0 + (int)xcd_block(blockIdx.x, G);
+    int n = HI;
+    for (int m = HI - 1; m >= LO; --m)
+        if (plan->item_start[m] <= it) n = m;
+    n = __builtin_amdgcn_readfirstlane(n);
+    ragged_dispatch<LO, ragged_class_waves(C)>(a, n, it, lds, std::make_integer_sequence<int, HI - LO + 1>{});
 }
 
 /* ------------------------------------------------------------------------ */
@@ -316,58 +356,62 @@ struct GroupLoc {
 /* systems of one grouped work item: one round of the workgroup */
 __host__ __device__ constexpr int grouped_per_item(int T) { return ragged_per_round(T); }
 
-template <int N, int T>
+template <int N, int T, int W>
 __device__ __forceinline__ bool grouped_try_lanes(const GroupDesc &g, int lanes, int local,
-                                                  int factors)
+                                                  int factors, double *lds)
 {
     if constexpr (ragged_lanes_ok(N, T)) {
         if (lanes == T) {
             const int64_t first = (int64_t)local * grouped_per_item(T);
             const int64_t rest = g.batch - first;
             const int cnt = (int)(rest < grouped_per_item(T) ? rest : grouped_per_item(T));
-            solve_item<N, T>(GroupLoc<N>{g, first}, cnt, factors);
+            solve_item<N, T, W>(GroupLoc<N>{g, first}, cnt, factors, lds);
             return true;
         }
     }
     return false;
 }
 
-template <int N>
-__device__ __forceinline__ bool grouped_try(const GroupDesc &g, int n, int local, int factors)
+template <int N, int W>
+__device__ __forceinline__ bool grouped_try(const GroupDesc &g, int n, int local, int factors,
+                                            double *lds)
 {
     if (n != N) return false;
     if constexpr (N > kRaggedSmallMax) {
-        (void)grouped_try_lanes<N, 16>(g, 16, local, factors); /* the only count compiled */
+        (void)grouped_try_lanes<N, 16, W>(g, 16, local, factors, lds); /* the only count compiled */
     } else {
         const int lanes = __builtin_amdgcn_readfirstlane(g.lanes);
-        (void)(grouped_try_lanes<N, 1>(g, lanes, local, factors) ||
-               grouped_try_lanes<N, 2>(g, lanes, local, factors) ||
-               grouped_try_lanes<N, 4>(g, lanes, local, factors) ||
-               grouped_try_lanes<N, 8>(g, lanes, local, factors) ||
-               grouped_try_lanes<N, 16>(g, lanes, local, factors));
+        (void)(grouped_try_lanes<N, 1, W>(g, lanes, local, factors, lds) ||
+               grouped_try_lanes<N, 2, W>(g, lanes, local, factors, lds) ||
+               grouped_try_lanes<N, 4, W>(g, lanes, local, factors, lds) ||
+               grouped_try_lanes<N, 8, W>(g, lanes, local, factors, lds) ||
+               grouped_try_lanes<N, 16, W>(g, lanes, local, factors, lds));
     }
     return true;
 }
 
-template <int LO, int... Ns>
+template <int LO, int W, int... Ns>
 __device__ __forceinline__ void grouped_dispatch(const GroupDesc &g, int n, int local, int factors,
-                                                 std::integer_sequence<int, Ns...>)
+                                                 double *lds, std::integer_sequence<int, Ns...>)
 {
-    (void)(grouped_try<LO + Ns>(g, n, local, factors) || ...);
+    (void)(grouped_try<LO + Ns, W>(g, n, local, factors, lds) || ...);
 }
 
-/* Work item `it` of a grouped launch over sizes LO..HI (all threads of the
- * workgroup): find its group (uniform), then solve its systems. */
-template <int LO, int HI>
+/* Work item `it` of a grouped launch over the sizes of class C (all threads of
+ * the workgroup): find its group (uniform), then solve its systems. */
+template <int C>
 __device__ __forceinline__ void grouped_run(const GroupedArgs &a, int it)
 {
+    constexpr int LO = ragged_class_lo(C), HI = ragged_class_hi(C);
+    __shared__ __align__(16) double lds[ragged_lds<LO, HI>()];
     int gi = 0;
     for (int k = 1; k < a.ngroups; ++k)
         if (it >= a.g[k].item0) gi = k;
     gi = __builtin_amdgcn_readfirstlane(gi);
     const GroupDesc &g = a.g[gi];
-    grouped_dispatch<LO>(g, __builtin_amdgcn_readfirstlane(g.n), it - g.item0, g.factors,
-                         std::make_integer_sequence<int, HI - LO + 1>{});
+    grouped_dispatch<LO, ragged_class_waves(C)>(g, __builtin_amdgcn_readfirstlane(g.n), it - g.item0,
+                                                g.factors, lds,
+                                                std::make_integer_sequence<int, HI - LO + 1>{});
 }
 
 /* Grouped kernels (grouped_c0.hip .. grouped_c2.hip), one per size class:
@@ -381,9 +425,6 @@ hipError_t grouped_c2_launch(const GroupedArgs &a, unsigned items, hipStream_t s
 hipError_t ragged_c0_launch(const RaggedArgs &a, unsigned grid, hipStream_t st);
 hipError_t ragged_c1_launch(const RaggedArgs &a, unsigned grid, hipStream_t st);
 hipError_t ragged_c2_launch(const RaggedArgs &a, unsigned grid, hipStream_t st);
-/* waves per SIMD each ragged class kernel is compiled for (its resident
- * grid is compute units x this) */
-__host__ __device__ constexpr int ragged_class_waves(int c) { return c == 0 ? 2 : 3; }
 
 }  // namespace lupp
 

@@ -129,7 +129,7 @@ int ragged_enqueue(RaggedPlan *plan, int32_t *sorted, const uint8_t *lanes, int6
                    const int32_t *n, const int64_t *offA, const int64_t *offB, double *A, double *b,
                    int32_t *ipiv, int32_t *info, bool factors, bool per_size, hipStream_t st)
 {
-    RaggedArgs a{batch, n, offA, offB, A, b, ipiv, info, factors ? 1 : 0, sorted, plan, {}};
+    RaggedArgs a{batch, n, offA, offB, A, b, ipiv, info, factors ? 1 : 0, sorted, plan, 0, {}};
     for (int m = 0; m <= 32; ++m) a.lanes[m] = m >= 1 ? lanes[m] : 1;
     /* grouping grid: at most 1024 workgroups of 256 threads, each a chunk */
     const int64_t full = (batch + 255) / 256;
@@ -141,14 +141,22 @@ int ragged_enqueue(RaggedPlan *plan, int32_t *sorted, const uint8_t *lanes, int6
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_err(e);
     if (!per_size) {
-        int dev = 0, cus = 256;
-        hipGetDevice(&dev);
-        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-        /* each class kernel with as many workgroups as stay resident: a CU
-         * holds 4 SIMDs x (waves per SIMD) waves, 4 waves per workgroup */
-        e = ragged_c0_launch(a, (unsigned)(cus * ragged_class_waves(0)), st);
-        if (e == hipSuccess) e = ragged_c1_launch(a, (unsigned)(cus * ragged_class_waves(1)), st);
-        if (e == hipSuccess) e = ragged_c2_launch(a, (unsigned)(cus * ragged_class_waves(2)), st);
+        /* one workgroup per work item, for as many items as a class can have:
+         * every system in its size with the fewest systems per item, and one
+         * item that is not full per size; in launches of at most kMaxItems */
+        constexpr int64_t kMaxItems = (int64_t)1 << 23;
+        hipError_t (*const launch[kRaggedClasses])(const RaggedArgs &, unsigned, hipStream_t) = {
+            ragged_c0_launch, ragged_c1_launch, ragged_c2_launch};
+        for (int c = 0; c < kRaggedClasses && e == hipSuccess; ++c) {
+            int per = kRaggedThreads;
+            for (int m = ragged_class_lo(c); m <= ragged_class_hi(c); ++m)
+                per = ragged_per_item(a.lanes[m]) < per ? ragged_per_item(a.lanes[m]) : per;
+            const int64_t most = batch / per + (ragged_class_hi(c) - ragged_class_lo(c) + 1);
+            for (int64_t i0 = 0; i0 < most && e == hipSuccess; i0 += kMaxItems) {
+                a.item0 = (int32_t)i0;
+                e = launch[c](a, (unsigned)(most - i0 < kMaxItems ? most - i0 : kMaxItems), st);
+            }
+        }
         return hip_err(e);
     }
     /* one launch per size: the host reads the plan (a synchronisation) */

@@ -1,13 +1,13 @@
-/* Ragged kernel of size class 1, sizes 17..23 (see kernels_ragged.h): 16-lane
- * segments need at most 164 VGPRs, so it runs 3 waves per SIMD. */
+/* Ragged kernel of size class 1, sizes 17..21 (see kernels_ragged.h): 120
+ * VGPRs, 4 waves per SIMD. */
 #include "kernels_ragged.h"
 
 namespace lupp {
 
 __global__ void __launch_bounds__(kRaggedThreads)
-    __attribute__((amdgpu_waves_per_eu(ragged_class_waves(1)))) k_ragged_c1(RaggedArgs a)
+    __attribute__((amdgpu_waves_per_eu(ragged_class_waves(1), ragged_class_waves(1)))) k_ragged_c1(RaggedArgs a)
 {
-    ragged_class_loop<1>(a);
+    ragged_class_item<1>(a);
 }
 
 hipError_t ragged_c1_launch(const RaggedArgs &a, unsigned grid, hipStream_t st)
