@@ -34,9 +34,10 @@
  *     with a pivot or numerator outside 2^-400 .. 2^400 (zeros included)
  *     takes true divisions instead.
  *
- * Measured (262144 systems of N(0, 1) entries, packed, strict mode, solution
- * only / with factors): n = 32: 1187 / 1264 -> 967 / 1002 us; n = 24: 703 /
- * 704 -> 561 / 567 us (16 lanes), 482 / 607 us (8 lanes).
+ * Measured (262144 systems of N(0, 1) entries, packed, strict mode, us, solution
+ * only / with factors; the ds_bpermute form -> this one): n = 32: 1187 / 1264 ->
+ * 850 / 932; n = 24: 703 / 704 -> 518 / 541 (16 lanes), 456 / 582 (8 lanes). At
+ * n = 32 the vector units are busy 73% of the time, LDS half of it.
  *
  * LDS traffic decides the shape of the broadcast: a masked ds_write_b128 costs
  * 13.7 cycles of the CU's LDS whatever the number of active lanes, a
@@ -174,6 +175,59 @@ __device__ __forceinline__ void masked_msub(uint64_t m, double l, double *a, con
     }
 }
 
+/* Both steps of a pair: a[i] -= l0 * u0[i] in the lanes of m0, then
+ * a[i] -= l1 * u1[i] in the lanes of m1, in one block (one change of the
+ * execution mask less than two blocks) */
+#define LUPP_MUL_SUB1(i) \
+    "v_mul_f64 %[t], %[h], %[w" #i "]\n\tv_add_f64 %[a" #i "], %[a" #i "], -%[t]\n\t"
+#define LUPP_FMA_SUB1(i) "v_fma_f64 %[a" #i "], -%[h], %[w" #i "], %[a" #i "]\n\t"
+#define LUPP_IN1 "s_mov_b64 exec, %[n]\n\t"
+#define LUPP_RD1(i) [w##i] "v"(w[i])
+template <bool kFMA, int C>
+__device__ __forceinline__ void masked_msub2(uint64_t m, double l, const double *u, uint64_t n,
+                                             double h, const double *w, double *a)
+{
+    double t;
+    if constexpr (C == 1) {
+        if constexpr (kFMA)
+            asm volatile(LUPP_IN LUPP_FMA_SUB(0) LUPP_IN1 LUPP_FMA_SUB1(0) LUPP_OUT
+                         : LUPP_RW(0)
+                         : [l] "v"(l), [h] "v"(h), LUPP_RD(0), LUPP_RD1(0), [m] "s"(m), [n] "s"(n));
+        else
+            asm volatile(LUPP_IN LUPP_MUL_SUB(0) LUPP_IN1 LUPP_MUL_SUB1(0) LUPP_OUT
+                         : LUPP_RW(0), [t] "=&v"(t)
+                         : [l] "v"(l), [h] "v"(h), LUPP_RD(0), LUPP_RD1(0), [m] "s"(m), [n] "s"(n));
+    } else if constexpr (C == 2) {
+        if constexpr (kFMA)
+            asm volatile(LUPP_IN LUPP_FMA_SUB(0) LUPP_FMA_SUB(1) LUPP_IN1 LUPP_FMA_SUB1(0) LUPP_FMA_SUB1(1) LUPP_OUT
+                         : LUPP_RW(0), LUPP_RW(1)
+                         : [l] "v"(l), [h] "v"(h), LUPP_RD(0), LUPP_RD(1), LUPP_RD1(0), LUPP_RD1(1),
+                           [m] "s"(m), [n] "s"(n));
+        else
+            asm volatile(LUPP_IN LUPP_MUL_SUB(0) LUPP_MUL_SUB(1) LUPP_IN1 LUPP_MUL_SUB1(0) LUPP_MUL_SUB1(1) LUPP_OUT
+                         : LUPP_RW(0), LUPP_RW(1), [t] "=&v"(t)
+                         : [l] "v"(l), [h] "v"(h), LUPP_RD(0), LUPP_RD(1), LUPP_RD1(0), LUPP_RD1(1),
+                           [m] "s"(m), [n] "s"(n));
+    } else if constexpr (C == 4) {
+        if constexpr (kFMA)
+            asm volatile(LUPP_IN LUPP_FMA_SUB(0) LUPP_FMA_SUB(1) LUPP_FMA_SUB(2) LUPP_FMA_SUB(3)
+                         LUPP_IN1 LUPP_FMA_SUB1(0) LUPP_FMA_SUB1(1) LUPP_FMA_SUB1(2) LUPP_FMA_SUB1(3) LUPP_OUT
+                         : LUPP_RW(0), LUPP_RW(1), LUPP_RW(2), LUPP_RW(3)
+                         : [l] "v"(l), [h] "v"(h), LUPP_RD(0), LUPP_RD(1), LUPP_RD(2), LUPP_RD(3),
+                           LUPP_RD1(0), LUPP_RD1(1), LUPP_RD1(2), LUPP_RD1(3), [m] "s"(m), [n] "s"(n));
+        else
+            asm volatile(LUPP_IN LUPP_MUL_SUB(0) LUPP_MUL_SUB(1) LUPP_MUL_SUB(2) LUPP_MUL_SUB(3)
+                         LUPP_IN1 LUPP_MUL_SUB1(0) LUPP_MUL_SUB1(1) LUPP_MUL_SUB1(2) LUPP_MUL_SUB1(3) LUPP_OUT
+                         : LUPP_RW(0), LUPP_RW(1), LUPP_RW(2), LUPP_RW(3), [t] "=&v"(t)
+                         : [l] "v"(l), [h] "v"(h), LUPP_RD(0), LUPP_RD(1), LUPP_RD(2), LUPP_RD(3),
+                           LUPP_RD1(0), LUPP_RD1(1), LUPP_RD1(2), LUPP_RD1(3), [m] "s"(m), [n] "s"(n));
+    } else if constexpr (C > 0) {
+        constexpr int H = C > 4 ? 4 : 2;
+        masked_msub2<kFMA, H>(m, l, u, n, h, w, a);
+        masked_msub2<kFMA, C - H>(m, l, u + H, n, h, w + H, a + H);
+    }
+}
+
 /* d = fma(e, y, q), d = y, in the lanes of m */
 __device__ __forceinline__ void masked_fma(uint64_t m, double &d, double e, double y, double q)
 {
@@ -210,6 +264,21 @@ __device__ __forceinline__ void masked_put4(uint64_t m, unsigned p, double x, do
                  "ds_write2_b64 %[p], %[z], %[w] offset0:%[o2] offset1:%[o3]\n\t" LUPP_OUT
                  :: [p] "v"(p), [x] "v"(x), [y] "v"(y), [z] "v"(z), [w] "v"(w), [m] "s"(m),
                     [o0] "n"(OFF), [o1] "n"(OFF + 1), [o2] "n"(OFF + 2), [o3] "n"(OFF + 3)
+                 : "memory");
+}
+
+template <int OFF>
+__device__ __forceinline__ void masked_put8(uint64_t m, unsigned p, double x0, double x1, double x2,
+                                            double x3, double x4, double x5, double x6, double x7)
+{
+    asm volatile(LUPP_IN "ds_write2_b64 %[p], %[x0], %[x1] offset0:%[o0] offset1:%[o1]\n\t"
+                 "ds_write2_b64 %[p], %[x2], %[x3] offset0:%[o2] offset1:%[o3]\n\t"
+                 "ds_write2_b64 %[p], %[x4], %[x5] offset0:%[o4] offset1:%[o5]\n\t"
+                 "ds_write2_b64 %[p], %[x6], %[x7] offset0:%[o6] offset1:%[o7]\n\t" LUPP_OUT
+                 :: [p] "v"(p), [x0] "v"(x0), [x1] "v"(x1), [x2] "v"(x2), [x3] "v"(x3), [x4] "v"(x4),
+                    [x5] "v"(x5), [x6] "v"(x6), [x7] "v"(x7), [m] "s"(m), [o0] "n"(OFF),
+                    [o1] "n"(OFF + 1), [o2] "n"(OFF + 2), [o3] "n"(OFF + 3), [o4] "n"(OFF + 4),
+                    [o5] "n"(OFF + 5), [o6] "n"(OFF + 6), [o7] "n"(OFF + 7)
                  : "memory");
 }
 
@@ -394,13 +463,21 @@ __device__ __forceinline__ int seg_getrf_solve(double (&a)[(N + T - 1) / T][N],
             const unsigned r = in_mask(h1[s]) ? rp + RS * 8 : rp;
             const uint64_t m = h0[s] | h1[s];
             masked_put_i32<IP + 4 * (k + 1)>(h1[s], rp, pos[s]);
-            static_for<0, (N + 1 - k + 3) / 4>(LUPP_SF(pc) {
-                constexpr int j = k + 4 * decltype(pc)::value;
-                auto val = [&](auto jc) __attribute__((always_inline)) -> double {
-                    constexpr int c = decltype(jc)::value;
-                    if constexpr (c < N) return a[s][c];
-                    else return b[s];
-                };
+            auto val = [&](auto jc) __attribute__((always_inline)) -> double {
+                constexpr int c = decltype(jc)::value;
+                if constexpr (c < N) return a[s][c];
+                else return b[s];
+            };
+            constexpr int cols = N + 1 - k, full = cols / 8 * 8;
+            static_for<0, cols / 8>(LUPP_SF(pc) {
+                constexpr int j = k + 8 * decltype(pc)::value;
+                masked_put8<j>(m, r, val(std::integral_constant<int, j>{}), val(std::integral_constant<int, j + 1>{}),
+                               val(std::integral_constant<int, j + 2>{}), val(std::integral_constant<int, j + 3>{}),
+                               val(std::integral_constant<int, j + 4>{}), val(std::integral_constant<int, j + 5>{}),
+                               val(std::integral_constant<int, j + 6>{}), val(std::integral_constant<int, j + 7>{}));
+            });
+            static_for<0, (cols - full + 3) / 4>(LUPP_SF(pc) {
+                constexpr int j = k + full + 4 * decltype(pc)::value;
                 const double x = val(std::integral_constant<int, j>{});
                 if constexpr (j + 3 <= N) {
                     masked_put4<j>(m, r, x, val(std::integral_constant<int, j + 1>{}),
@@ -442,8 +519,7 @@ __device__ __forceinline__ int seg_getrf_solve(double (&a)[(N + T - 1) / T][N],
         masked_msub<kFMA, 1>(n0, p1.x, y1, y0);
         static_for<0, K>(LUPP_SF(sc) {
             constexpr int s = decltype(sc)::value;
-            masked_msub<kFMA, 1>(m0[s], a[s][k], &b[s], y0);
-            masked_msub<kFMA, 1>(m1[s], a[s][k + 1], &b[s], y1);
+            masked_msub2<kFMA, 1>(m0[s], a[s][k], y0, m1[s], a[s][k + 1], y1, &b[s]);
         });
         static_for<0, NC>(LUPP_SF(cc) {
             constexpr int c = decltype(cc)::value;
@@ -453,8 +529,8 @@ __device__ __forceinline__ int seg_getrf_solve(double (&a)[(N + T - 1) / T][N],
             masked_msub<kFMA, j1 - j0>(n0, p1.x, u1[c & 1], u0[c & 1]);
             static_for<0, K>(LUPP_SF(sc) {
                 constexpr int s = decltype(sc)::value;
-                masked_msub<kFMA, j1 - j0>(m0[s], a[s][k], &a[s][j0], u0[c & 1]);
-                masked_msub<kFMA, j1 - j0>(m1[s], a[s][k + 1], &a[s][j0], u1[c & 1]);
+                masked_msub2<kFMA, j1 - j0>(m0[s], a[s][k], u0[c & 1], m1[s], a[s][k + 1], u1[c & 1],
+                                            &a[s][j0]);
             });
         });
         seg_order();
@@ -541,6 +617,10 @@ __device__ __forceinline__ int seg_getrf_solve(double (&a)[(N + T - 1) / T][N],
 #undef LUPP_FMA_SUB
 #undef LUPP_RW
 #undef LUPP_RD
+#undef LUPP_IN1
+#undef LUPP_MUL_SUB1
+#undef LUPP_FMA_SUB1
+#undef LUPP_RD1
 
 }  // namespace lupp
 
