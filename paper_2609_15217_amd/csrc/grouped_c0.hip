@@ -7,7 +7,7 @@ namespace lupp {
 __global__ void __launch_bounds__(kRaggedThreads) __attribute__((amdgpu_waves_per_eu(ragged_class_waves(0), ragged_class_waves(0))))
     k_grouped_c0(GroupedArgs a)
 {
-    grouped_run<0>(a, (int)xcd_block(blockIdx.x, gridDim.x));
+    grouped_run<0>(a, (int)blockIdx.x);
 }
 
 hipError_t grouped_c0_launch(const GroupedArgs &a, unsigned items, hipStream_t st)

@@ -7,7 +7,7 @@ namespace lupp {
 __global__ void __launch_bounds__(kRaggedThreads) __attribute__((amdgpu_waves_per_eu(ragged_class_waves(1), ragged_class_waves(1))))
     k_grouped_c1(GroupedArgs a)
 {
-    grouped_run<1>(a, (int)xcd_block(blockIdx.x, gridDim.x));
+    grouped_run<1>(a, (int)blockIdx.x);
 }
 
 hipError_t grouped_c1_launch(const GroupedArgs &a, unsigned items, hipStream_t st)

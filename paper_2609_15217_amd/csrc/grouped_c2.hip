@@ -7,7 +7,7 @@ namespace lupp {
 __global__ void __launch_bounds__(kRaggedThreads) __attribute__((amdgpu_waves_per_eu(ragged_class_waves(2), ragged_class_waves(2))))
     k_grouped_c2(GroupedArgs a)
 {
-    grouped_run<2>(a, (int)xcd_block(blockIdx.x, gridDim.x));
+    grouped_run<2>(a, (int)blockIdx.x);
 }
 
 hipError_t grouped_c2_launch(const GroupedArgs &a, unsigned items, hipStream_t st)
