@@ -36,14 +36,16 @@ __host__ __device__ constexpr int ragged_class_of(int n) { return n >= 22 ? 0 : 
 /* waves per SIMD each class kernel is compiled for */
 __host__ __device__ constexpr int ragged_class_waves(int c) { return c == 0 ? 3 : 4; }
 
+/* grouping kernels: at most this many workgroups of this many threads */
+constexpr int kGroupBlocks = 256, kGroupThreads = 1024;
+
 struct RaggedPlan {
     int32_t count[33];      /* systems of each size */
     int32_t bin_start[33];  /* first index of each size in `sorted` */
-    int32_t cursor[33];     /* scatter cursors */
     int32_t item_start[33]; /* first work item of each size */
     /* work items of class c: class_start[c] .. class_start[c + 1] - 1 */
     int32_t class_start[kRaggedClasses + 1];
-    int32_t bad;            /* systems with n outside 1..32 */
+    int32_t part[kGroupBlocks][32]; /* systems of size m + 1 in each grouping chunk */
 };
 
 struct RaggedArgs {

@@ -1,97 +1,101 @@
 /* Ragged (mixed-size) batches: device-side grouping by size and one launch
  * per size class (see kernels_ragged.h). */
+#include <cstddef>
 #include <cstring>
 
 #include "kernels_ragged.h"
 
 namespace lupp {
 
-/* clear the per-call counters (a kernel rather than a memset, so the whole
- * sequence can be captured in a graph) */
-__global__ void k_ragged_zero(RaggedPlan *plan)
-{
-    const int i = threadIdx.x;
-    if (i < 33) plan->count[i] = 0;
-    if (i == 0) plan->bad = 0;
-}
-
-/* Grouping by size. Workgroup g owns the contiguous chunk of systems
- * [g*chunk, (g+1)*chunk), chunk a multiple of 256: a few hundred workgroups,
- * so the per-size global atomics (one per workgroup and size) stay few. */
+/* Grouping by size, in two kernels. Workgroup g owns the contiguous chunk of
+ * systems [g*chunk, (g+1)*chunk), chunk a multiple of the workgroup: the first
+ * kernel counts the sizes of every chunk (RaggedPlan::part), the second sums
+ * these counts for the plan and for the place of its own systems in the bins.
+ * No global atomics and nothing to clear; every call writes all it reads.
+ *
+ * What it costs is latency, not the 12 bytes per system it moves: a launch of
+ * a few microseconds per kernel, atomics of many workgroups on 32 addresses.
+ * Hence few, large workgroups, and the 32-entry plan by scans of one wave in
+ * every workgroup of the second kernel. Four kernels (clear, count with
+ * global atomics on up to 1024 workgroups of 256, plan by one thread, scatter)
+ * took 22 us for 20,000 systems, 50 for 250,000 and 60 for 2,000,000; these two
+ * take 10, 10 and 18. */
 __device__ __forceinline__ void ragged_chunk(const RaggedArgs &a, int64_t &c0, int64_t &c1)
 {
-    const int64_t chunk = ((a.batch + gridDim.x - 1) / gridDim.x + 255) / 256 * 256;
+    const int64_t chunk = ((a.batch + gridDim.x - 1) / gridDim.x + kGroupThreads - 1) / kGroupThreads *
+                          kGroupThreads;
     c0 = (int64_t)blockIdx.x * chunk;
     c1 = c0 + chunk < a.batch ? c0 + chunk : a.batch;
 }
 
-/* size histogram, privatised in LDS */
-__global__ void __launch_bounds__(256) k_ragged_hist(RaggedArgs a)
+/* systems of each size in the chunk, privatised in LDS */
+__global__ void __launch_bounds__(kGroupThreads) k_ragged_hist(RaggedArgs a)
 {
-    __shared__ int h[34];
-    if (threadIdx.x < 34) h[threadIdx.x] = 0;
+    __shared__ int h[32];
+    if (threadIdx.x < 32) h[threadIdx.x] = 0;
     __syncthreads();
     int64_t c0, c1;
     ragged_chunk(a, c0, c1);
-    for (int64_t s = c0 + threadIdx.x; s < c1; s += blockDim.x) {
+#pragma unroll 4
+    for (int64_t s = c0 + threadIdx.x; s < c1; s += kGroupThreads) {
         const int n = a.n[s];
-        atomicAdd(&h[(n >= 1 && n <= 32) ? n : 0], 1);
+        if (n >= 1 && n <= 32) atomicAdd(&h[n - 1], 1);
     }
     __syncthreads();
-    if (threadIdx.x >= 1 && threadIdx.x <= 32 && h[threadIdx.x] != 0)
-        atomicAdd(&a.plan->count[threadIdx.x], h[threadIdx.x]);
-    if (threadIdx.x == 0 && h[0] != 0) atomicAdd(&a.plan->bad, h[0]);
+    if (threadIdx.x < 32) a.plan->part[blockIdx.x][threadIdx.x] = h[threadIdx.x];
 }
 
-/* bins in descending size, work items per bin (their size follows the lane
- * count of the size), class boundaries */
-__global__ void k_ragged_plan(RaggedArgs a)
+/* The plan, bins in descending size (work items per bin follow the lane count
+ * of the size), and the system indices in their bins: chunk by chunk within a
+ * bin, in any order within a chunk (systems are independent). */
+__global__ void __launch_bounds__(kGroupThreads) k_ragged_scatter(RaggedArgs a)
 {
-    if (threadIdx.x != 0) return;
+    /* by size - 1: systems, those of earlier chunks, next index of this chunk */
+    __shared__ int total[32], before[32], next[32];
     RaggedPlan *plan = a.plan;
-    int start = 0, items = 0;
-    for (int n = 32; n >= 1; --n) {
-        if (n == ragged_class_hi(ragged_class_of(n))) plan->class_start[ragged_class_of(n)] = items;
-        plan->bin_start[n] = start;
-        plan->item_start[n] = items;
-        plan->cursor[n] = 0;
-        const int c = plan->count[n];
-        const int per = ragged_per_item(a.lanes[n]);
-        start += c;
-        items += (c + per - 1) / per;
+    const int tid = (int)threadIdx.x;
+    if (tid < 32) total[tid] = before[tid] = 0;
+    __syncthreads();
+    {
+        int tot = 0, bef = 0;
+#pragma unroll 4
+        for (int g = tid >> 5; g < (int)gridDim.x; g += kGroupThreads / 32) {
+            const int v = plan->part[g][tid & 31];
+            tot += v;
+            bef += g < (int)blockIdx.x ? v : 0;
+        }
+        atomicAdd(&total[tid & 31], tot);
+        atomicAdd(&before[tid & 31], bef);
     }
-    plan->class_start[kRaggedClasses] = items;
-}
-
-/* scatter system indices into their bins: each workgroup counts its chunk,
- * reserves one range per size with a single global atomic, then places its
- * systems (the order inside a bin does not matter: systems are independent) */
-__global__ void __launch_bounds__(256) k_ragged_scatter(RaggedArgs a)
-{
-    __shared__ int cnt[33], base[33], fill[33];
-    if (threadIdx.x < 33) {
-        cnt[threadIdx.x] = 0;
-        fill[threadIdx.x] = 0;
+    __syncthreads();
+    if (tid < 32) {
+        /* lane i holds size 32 - i: inclusive scans over descending sizes */
+        const int n = 32 - tid, c = total[n - 1];
+        const int per = ragged_per_item(a.lanes[n]);
+        const int it = (c + per - 1) / per;
+        int cs = c, is = it;
+        for (int d = 1; d < 32; d *= 2) {
+            const int cu = __shfl_up(cs, d, 32), iu = __shfl_up(is, d, 32);
+            cs += tid >= d ? cu : 0;
+            is += tid >= d ? iu : 0;
+        }
+        next[n - 1] = cs - c + before[n - 1];
+        if (blockIdx.x == 0) {
+            plan->count[n] = c;
+            plan->bin_start[n] = cs - c;
+            plan->item_start[n] = is - it;
+            if (n == ragged_class_hi(ragged_class_of(n))) plan->class_start[ragged_class_of(n)] = is - it;
+            if (n == 1) plan->class_start[kRaggedClasses] = is;
+        }
     }
     __syncthreads();
     int64_t c0, c1;
     ragged_chunk(a, c0, c1);
-    for (int64_t s = c0 + threadIdx.x; s < c1; s += blockDim.x) {
+#pragma unroll 4
+    for (int64_t s = c0 + tid; s < c1; s += kGroupThreads) {
         const int n = a.n[s];
-        if (n >= 1 && n <= 32) atomicAdd(&cnt[n], 1);
+        if (n >= 1 && n <= 32) a.sorted[atomicAdd(&next[n - 1], 1)] = (int32_t)s;
         else a.info[s] = -1;
-    }
-    __syncthreads();
-    if (threadIdx.x >= 1 && threadIdx.x <= 32)
-        base[threadIdx.x] =
-            cnt[threadIdx.x] ? atomicAdd(&a.plan->cursor[threadIdx.x], cnt[threadIdx.x]) : 0;
-    __syncthreads();
-    for (int64_t s = c0 + threadIdx.x; s < c1; s += blockDim.x) {
-        const int n = a.n[s];
-        if (n >= 1 && n <= 32) {
-            const int p = atomicAdd(&fill[n], 1);
-            a.sorted[a.plan->bin_start[n] + base[n] + p] = (int32_t)s;
-        }
     }
 }
 
@@ -100,7 +104,7 @@ hipError_t ragged_one_launch(int n, const RaggedArgs &a, int items, hipStream_t 
 /* Workspace of the allocating entry point. Calls on one context may come on
  * different streams: `done` is recorded after each call's last kernel, and
  * the next call on another stream waits for it before its grouping kernels
- * reset the plan and rewrite `sorted` (which the earlier call's solve
+ * rewrite the plan and `sorted` (which the earlier call's solve
  * kernels may still be reading). */
 struct RaggedWs {
     RaggedPlan *plan = nullptr;
@@ -131,13 +135,10 @@ int ragged_enqueue(RaggedPlan *plan, int32_t *sorted, const uint8_t *lanes, int6
 {
     RaggedArgs a{batch, n, offA, offB, A, b, ipiv, info, factors ? 1 : 0, sorted, plan, 0, {}};
     for (int m = 0; m <= 32; ++m) a.lanes[m] = m >= 1 ? lanes[m] : 1;
-    /* grouping grid: at most 1024 workgroups of 256 threads, each a chunk */
-    const int64_t full = (batch + 255) / 256;
-    const unsigned blocks = (unsigned)(full < 1024 ? full : 1024);
-    hipLaunchKernelGGL(k_ragged_zero, dim3(1), dim3(64), 0, st, plan);
-    hipLaunchKernelGGL(k_ragged_hist, dim3(blocks), dim3(256), 0, st, a);
-    hipLaunchKernelGGL(k_ragged_plan, dim3(1), dim3(64), 0, st, a);
-    hipLaunchKernelGGL(k_ragged_scatter, dim3(blocks), dim3(256), 0, st, a);
+    const int64_t full = (batch + kGroupThreads - 1) / kGroupThreads;
+    const unsigned blocks = (unsigned)(full < kGroupBlocks ? full : kGroupBlocks);
+    hipLaunchKernelGGL(k_ragged_hist, dim3(blocks), dim3(kGroupThreads), 0, st, a);
+    hipLaunchKernelGGL(k_ragged_scatter, dim3(blocks), dim3(kGroupThreads), 0, st, a);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_err(e);
     if (!per_size) {
@@ -161,7 +162,7 @@ int ragged_enqueue(RaggedPlan *plan, int32_t *sorted, const uint8_t *lanes, int6
     }
     /* one launch per size: the host reads the plan (a synchronisation) */
     RaggedPlan h;
-    e = hipMemcpyAsync(&h, plan, sizeof(h), hipMemcpyDeviceToHost, st);
+    e = hipMemcpyAsync(&h, plan, offsetof(RaggedPlan, part), hipMemcpyDeviceToHost, st);
     if (e == hipSuccess) e = hipStreamSynchronize(st);
     if (e != hipSuccess) return hip_err(e);
     for (int m = 32; m >= 1; --m) {

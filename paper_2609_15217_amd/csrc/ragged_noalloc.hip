@@ -61,8 +61,8 @@ int noalloc_ragged_enqueue(int device, const uint8_t *lanes, int64_t batch, cons
     }
     RaggedPlan *plan = static_cast<RaggedPlan *>(base);
     int32_t *sorted = reinterpret_cast<int32_t *>(static_cast<unsigned char *>(base) + kNoAllocPlanBytes);
-    /* the zero kernel clears the plan's counters: the array keeps the last
-     * call's contents */
+    /* the array keeps the last call's contents; every call writes all of the
+     * plan that it reads */
     return ragged_enqueue(plan, sorted, lanes, batch, n, offA, offB, A, b, ipiv, info, factors,
                           false, st);
 }
