@@ -148,7 +148,7 @@ hipError_t launch_lanes(const SolveArgs &a, int layout, bool factors, int wpb, h
     LaunchFn lanes_fn_##N##_##T() { return launch_lanes<N, T>; }                   \
     const void *lanes_sym_##N##_##T(int layout)                                    \
     {                                                                              \
-        return layout == LUPP_SOA ? reinterpret_cast<const void *>(&k_seg_soa<N, T, false>) \
+        return layout == LUPP_SOA ? reinterpret_cast<const void *>(&k_seg_soa<N, T, false, 16>) \
                                   : reinterpret_cast<const void *>(&k_seg<N, T, false>); \
     }                                                                              \
     }

@@ -1,7 +1,8 @@
 /* Lanes-per-system batched solve with tile-local pivoting for the interleaved
  * (SoA) layout (strict and FMA solves with textbook pivoting: the same staging
- * in kernels_seg_soa.h), with the global traffic staged through LDS (Section 3: coalesced accesses to the
- * batch; Section 3.2: several rows per thread, several systems per wave).
+ * in kernels_seg_soa.h), with the global traffic staged through LDS (Section 3:
+ * coalesced accesses to the batch; Section 3.2: several rows per thread,
+ * several systems per wave).
  *
  * The solve itself is the one of k_lanes (T lanes per system, K = ceil(n/T)
  * rows per lane, logical pivoting). What differs is how the matrices move
@@ -36,10 +37,11 @@ namespace lupp {
 
 __host__ __device__ constexpr int ilog2c(int v) { return v <= 1 ? 0 : 1 + ilog2c(v / 2); }
 
-template <int N, int T>
+/* SYS: systems per workgroup (more where a wave alone holds more) */
+template <int N, int T, int SYS = 16>
 struct soa_shape {
     static constexpr int SPW = 64 / T;                   /* systems per wave */
-    static constexpr int S = SPW > 16 ? SPW : 16;        /* systems per workgroup */
+    static constexpr int S = SPW > SYS ? SPW : SYS;      /* systems per workgroup */
     static constexpr int WPB = S / SPW;                  /* waves per workgroup */
     static constexpr int NT = 64 * WPB;                  /* threads = S * T */
     static constexpr int K = (N + T - 1) / T;
@@ -63,10 +65,10 @@ struct soa_shape {
     static_assert(NT == S * T, "shape");
 };
 
-template <int N, int T>
+template <int N, int T, int SYS = 16>
 __device__ __forceinline__ int soa_sw(int i)
 {
-    using Sh = soa_shape<N, T>;
+    using Sh = soa_shape<N, T, SYS>;
     return ((i >> Sh::SH) << Sh::LOG_SPH) & (Sh::S - 1);
 }
 

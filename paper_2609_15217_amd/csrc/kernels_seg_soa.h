@@ -3,7 +3,8 @@
  * moves the matrices of 16 consecutive systems through LDS in whole 128-byte
  * lines) around the solver of lupp_segments.h. Measured against the
  * ds_bpermute solver in the same staging: see kernels_seg.h; one workgroup
- * holds 16/(64/T) waves, whose solver records reuse the staging tile. */
+ * holds 16/(64/T) waves, whose solver records reuse the staging tile.
+ * SYS = 32 systems, two lines per matrix element: see seg_soa_systems. */
 #ifndef LUPP_KERNELS_SEG_SOA_H
 #define LUPP_KERNELS_SEG_SOA_H
 
@@ -12,12 +13,32 @@
 
 namespace lupp {
 
-template <int N, int T, bool F>
-__global__ void __launch_bounds__((soa_shape<N, T>::NT))
+/* Systems per workgroup. Writing the factors is bound by memory, and 256
+ * contiguous bytes per element instead of 128 are written faster, above all
+ * where ldbatch is no multiple of 16, so that every row starts inside a line,
+ * or a power of two. Measured with 8 lanes, 16 -> 32 systems, us, at 2^20
+ * systems with ldbatch 2^20 + 192, 300007 dense and 2^19 dense: n = 14:
+ * 781 -> 731, 273 -> 238, 428 -> 384; n = 16: 1031 -> 935, 356 -> 308,
+ * 553 -> 487; n = 18: 1341 -> 1341, 424 -> 403, 737 -> 686; n = 20:
+ * 1585 -> 1596, 526 -> 482, 903 -> 827. The line lies where that no longer
+ * holds for all of them: n = 17 (24 staged rows of 17): 1220 -> 1248,
+ * 380 -> 376, 684 -> 641; n = 22: 2020 -> 2136, 633 -> 647, 1142 -> 1117;
+ * n = 24: 2308 -> 2388, 764 -> 741, 1344 -> 1271; n = 13 and less did not
+ * change (249 -> 247). Without the factors the larger workgroup only waits
+ * longer at its barriers (n = 24: 1945 -> 2055 and 586 -> 618), and with 16
+ * lanes its eight waves would be the only ones of a compute unit. */
+template <int N, int T>
+constexpr int seg_soa_systems(bool factors)
+{
+    return factors && T == 8 && N >= 14 && N <= 20 && N != 17 ? 32 : 16;
+}
+
+template <int N, int T, bool F, int SYS>
+__global__ void __launch_bounds__((soa_shape<N, T, SYS>::NT))
     __attribute__((amdgpu_waves_per_eu(seg_shape<N, T>::W, seg_shape<N, T>::W)))
     k_seg_soa(SolveArgs a, int factors)
 {
-    using Sh = soa_shape<N, T>;
+    using Sh = soa_shape<N, T, SYS>;
     constexpr int S = Sh::S, K = Sh::K, NP = Sh::NP, CJ = Sh::CJ, NCH = Sh::NCH;
     constexpr int QB = NP / T; /* cooperative accesses per column and thread */
     /* the staging tile; between the staging phases each wave's share holds its
@@ -70,9 +91,9 @@ __global__ void __launch_bounds__((soa_shape<N, T>::NT))
         return (ib + T <= N || ci0 < N - ib) ? v : kOutOfRange;
     };
     /* LDS index of the cooperative element (chunk column c, row block ib) */
-    auto cidx = [&](int c, int ib) { const int i = ci0 + ib; return (c * NP + i) * S + (yw ^ soa_sw<N, T>(i)); };
+    auto cidx = [&](int c, int ib) { const int i = ci0 + ib; return (c * NP + i) * S + (yw ^ soa_sw<N, T, SYS>(i)); };
     /* LDS index of a lane-side element (chunk column c, row i) */
-    auto lidx = [&](int c, int i) { return (c * NP + i) * S + (yl ^ soa_sw<N, T>(i)); };
+    auto lidx = [&](int c, int i) { return (c * NP + i) * S + (yl ^ soa_sw<N, T, SYS>(i)); };
 
     /* ---------------------------------------------------------- load */
     double m[K][N];
@@ -207,21 +228,29 @@ __global__ void __launch_bounds__((soa_shape<N, T>::NT))
     }
 }
 
+template <int N, int T, int SYS>
+hipError_t launch_seg_soa(const SolveArgs &a, bool factors, hipStream_t st)
+{
+    using Sh = soa_shape<N, T, SYS>;
+    const dim3 grid((unsigned)((a.batch + Sh::S - 1) / Sh::S));
+    const dim3 block(Sh::NT);
+    if (a.fma) hipLaunchKernelGGL((k_seg_soa<N, T, true, SYS>), grid, block, 0, st, a, (int)factors);
+    else hipLaunchKernelGGL((k_seg_soa<N, T, false, SYS>), grid, block, 0, st, a, (int)factors);
+    return hipGetLastError();
+}
+
 template <int N, int T>
 hipError_t launch_seg(const SolveArgs &a, int layout, bool factors, int wpb, hipStream_t st)
 {
-    const bool soa = layout == LUPP_SOA;
+    if (layout == LUPP_SOA)
+        return factors ? launch_seg_soa<N, T, seg_soa_systems<N, T>(true)>(a, factors, st)
+                       : launch_seg_soa<N, T, seg_soa_systems<N, T>(false)>(a, factors, st);
     const int w = wpb > 0 ? wpb : 4;
-    const int64_t per_block = soa ? soa_shape<N, T>::S : (int64_t)w * (64 / T);
+    const int64_t per_block = (int64_t)w * (64 / T);
     const dim3 grid((unsigned)((a.batch + per_block - 1) / per_block));
-    const dim3 block(soa ? soa_shape<N, T>::NT : 64 * w);
-    if (soa) {
-        if (a.fma) hipLaunchKernelGGL((k_seg_soa<N, T, true>), grid, block, 0, st, a, (int)factors);
-        else hipLaunchKernelGGL((k_seg_soa<N, T, false>), grid, block, 0, st, a, (int)factors);
-    } else {
-        if (a.fma) hipLaunchKernelGGL((k_seg<N, T, true>), grid, block, 0, st, a, (int)factors);
-        else hipLaunchKernelGGL((k_seg<N, T, false>), grid, block, 0, st, a, (int)factors);
-    }
+    const dim3 block(64 * w);
+    if (a.fma) hipLaunchKernelGGL((k_seg<N, T, true>), grid, block, 0, st, a, (int)factors);
+    else hipLaunchKernelGGL((k_seg<N, T, false>), grid, block, 0, st, a, (int)factors);
     return hipGetLastError();
 }
 

@@ -110,6 +110,20 @@ def test_half_width_kernels(L, ctx, n):
         assert_bits(ref, *got[:4], b)
 
 
+@pytest.mark.parametrize("batch", [1, 15, 16, 17, 31, 32, 33, 65])
+@pytest.mark.parametrize("n", [14, 15, 16])
+def test_interleaved_factors_by_32_systems(L, ctx, n, batch):
+    """Full and partial workgroups of the interleaved kernels that write the
+    factors with 8 lanes per system, dense and padded."""
+    A, b, _ = systems(n, batch, seed=7900 + n)
+    for fma in (False, True):
+        ref = oracle.gesv_batch_mode(A, b, fma=fma, threads=4)
+        for pad in (0, 5):
+            got = gpu_solve(L, ctx, A, b, L.LUPP_SOA, L.LUPP_VARIANT_LANES, 8, fma=fma, stride_pad=pad)
+            assert got[4]
+            assert_bits(ref, *got[:4], b)
+
+
 def test_caller_chosen_entries_hold(L):
     """An entry the caller set serves solve-only calls too."""
     ctx = L.Context(0)
