@@ -201,8 +201,8 @@ int lupp_batched_solve_ragged_noalloc(lupp_ctx *ctx, int64_t batch, const int32_
  * lupp_ragged_lanes_supported(n, lanes) accepts: 1 (one thread per system,
  * n <= 5), 2 (n = 2..4), 4 (n = 3..8), 8 (n = 5..16) and 16 (n >= 9).
  * 32 lanes (measured slower than 16 for every n >= 17) and 64 (half of a
- * wave64 without a row for any n <= 32) are not built. A context starts from the table the autotuner
- * measured on gfx950. lupp_ragged_lanes_supported: 1 or 0 (host-only, no
+ * wave64 without a row for any n <= 32) are not built. A context starts from
+ * the table the autotuner measured on gfx950. lupp_ragged_lanes_supported: 1 or 0 (host-only, no
  * device needed). lupp_set_ragged_lanes: 0, -2 for n outside 1..32, -3 for
  * an unsupported lane count. lupp_get_ragged_lanes: the lane count, or -2. */
 int lupp_ragged_lanes_supported(int n, int lanes);
@@ -239,8 +239,8 @@ int lupp_get_pivoting(const lupp_ctx *ctx, int *tile, double *threshold);
  * (LUPP_VARIANT_AUTO restores the size-aware dispatch table). lanes is the
  * segment width for LUPP_VARIANT_LANES (2, 4, 8, 16 or 32), wpb the number of
  * wave64s per workgroup (1, 2 or 4; 0 = default). In the SoA layout the lanes
- * variant has a fixed workgroup of 16 systems (staged through LDS) and
- * ignores wpb. Returns LUPP_E_UNSUPPORTED
+ * variant's workgroups hold 8, 16 or 32 systems (staged through LDS), by the
+ * size and the batch, and ignore wpb. Returns LUPP_E_UNSUPPORTED
  * if a later call's n cannot be served by the forced variant. */
 int lupp_force_variant(lupp_ctx *ctx, int variant, int lanes, int wpb);
 

@@ -4,7 +4,8 @@
  * lines) around the solver of lupp_segments.h. Measured against the
  * ds_bpermute solver in the same staging: see kernels_seg.h; one workgroup
  * holds 16/(64/T) waves, whose solver records reuse the staging tile.
- * SYS = 32 systems, two lines per matrix element: see seg_soa_systems. */
+ * Other numbers of systems per workgroup: see seg_soa_systems (32) and
+ * seg_soa_by_8. */
 #ifndef LUPP_KERNELS_SEG_SOA_H
 #define LUPP_KERNELS_SEG_SOA_H
 
@@ -239,9 +240,36 @@ hipError_t launch_seg_soa(const SolveArgs &a, bool factors, hipStream_t st)
     return hipGetLastError();
 }
 
+/* Whether an interleaved batch with 16 or 32 lanes runs 8 systems per
+ * workgroup. A small batch is bound by the steps' chain and by the row writes
+ * of one compute unit's LDS, which all its waves share: half the waves per
+ * workgroup spread better over the 256 compute units. Each line is then read
+ * by two workgroups, neighbours on one XCD, the second time from its L2.
+ * Measured, us, 16 -> 8 systems, solution only (with the factors alike):
+ * 32 lanes, 1000 / 4096 / 5003 / 10000 / 30000 systems: n = 21: 20.9 -> 15.8,
+ * 20.4 -> 20.2, 29.8 -> 26.2, 36.0 -> 31.8, 77 -> 71; n = 32: 33.2 -> 23.2,
+ * 32.5 -> 32.7, 52.5 -> 44.6, 68 -> 58, 155 -> 140. 16 lanes: n = 21:
+ * 21.4 -> 17.8, 22.1 -> 22.9, 30.2 -> 27.9, 34.7 -> 31.9, 70 -> 68; n = 32:
+ * 34.3 -> 28.3, 34.9 -> 38.4, 53.5 -> 48.6, 63 -> 58, 136 -> 133, and 16000
+ * systems 81 -> 87: with 16 lanes only where the busiest compute unit gets an
+ * eighth fewer systems. From 32768 systems on the dispatcher has other
+ * entries. The strides must keep a wave's 8 rows within 2^31 bytes (16
+ * systems: 4 rows). */
+template <int T>
+bool seg_soa_by_8(const SolveArgs &a)
+{
+    constexpr int64_t kCUs = 256, kSmall = 32768, kSpan = (int64_t)1 << 31;
+    if (a.batch >= kSmall || (7 * a.sA + 8) * 8 >= kSpan || (7 * a.sB + 8) * 8 >= kSpan) return false;
+    if (T == 32) return true;
+    auto busiest = [&](int64_t s) { return ((a.batch + s - 1) / s + kCUs - 1) / kCUs * s; };
+    return busiest(8) * 8 <= busiest(16) * 7;
+}
+
 template <int N, int T>
 hipError_t launch_seg(const SolveArgs &a, int layout, bool factors, int wpb, hipStream_t st)
 {
+    if constexpr (T >= 16)
+        if (layout == LUPP_SOA && seg_soa_by_8<T>(a)) return launch_seg_soa<N, T, 8>(a, factors, st);
     if (layout == LUPP_SOA)
         return factors ? launch_seg_soa<N, T, seg_soa_systems<N, T>(true)>(a, factors, st)
                        : launch_seg_soa<N, T, seg_soa_systems<N, T>(false)>(a, factors, st);

@@ -124,6 +124,21 @@ def test_interleaved_factors_by_32_systems(L, ctx, n, batch):
             assert_bits(ref, *got[:4], b)
 
 
+@pytest.mark.parametrize("n,lanes", [(9, 16), (16, 16), (21, 16), (32, 16), (17, 32), (32, 32)])
+@pytest.mark.parametrize("batch", [1, 7, 8, 9, 17, 2049, 4097])
+def test_interleaved_by_8_systems(L, ctx, n, lanes, batch):
+    """Small interleaved batches in workgroups of 8 systems: full and partial
+    workgroups, on both sides of what fits the compute units once."""
+    A, b, _ = systems(n, batch, seed=8000 + n)
+    for fma in (False, True):
+        ref = oracle.gesv_batch_mode(A, b, fma=fma, threads=8)
+        for keep in (False, True):
+            got = gpu_solve(L, ctx, A, b, L.LUPP_SOA, L.LUPP_VARIANT_LANES, lanes, fma=fma,
+                            keep_a=keep, stride_pad=3)
+            assert got[4]
+            assert_bits(ref, *got[:4], b, **({"A": A} if keep else {}))
+
+
 def test_caller_chosen_entries_hold(L):
     """An entry the caller set serves solve-only calls too."""
     ctx = L.Context(0)
