@@ -250,7 +250,8 @@ int lupp_force_variant(lupp_ctx *ctx, int variant, int lanes, int wpb);
  * factors written. Until the caller sets or autotunes an entry, batches from
  * 32768 systems on may run a kernel that measured faster without the factors
  * (LUPP_KEEP_A) or in the interleaved layout, among them widths that cannot be
- * forced; results do not depend on it. */
+ * forced, and tile-local pivoting may run entries of its own; results do not
+ * depend on it. */
 int lupp_set_dispatch(lupp_ctx *ctx, int n, int layout, int64_t batch, int variant, int lanes,
                       int wpb);
 int lupp_get_dispatch(lupp_ctx *ctx, int n, int layout, int64_t batch, int *variant, int *lanes,

@@ -113,6 +113,20 @@ static Choice auto_choice(int n, int layout, int bucket, bool factors, const Cho
     return c;
 }
 
+/* Tile-local pivoting runs other kernels (kernels_lanes.h) than those the
+ * table's entries were measured with. Packed batches of n = 9..16 are faster
+ * with two rows per lane there (tile 4, 524288 systems, factors, us, table's
+ * entry -> this: n = 9: 236 -> 212; n = 12: 371 -> 315; n = 16: 582 -> 487),
+ * small interleaved ones from n = 22 on with 16 lanes (4096 systems: n = 28:
+ * 40.5 -> 39.3; n = 32: 47.9 -> 47.0; n = 17 would lose, 22.9 -> 23.4). The
+ * other entries measured within 3% of the best. */
+static Choice tiled_choice(int n, int layout, int bucket, const Choice &c)
+{
+    if (layout == LUPP_SOA)
+        return bucket == 0 && n >= 22 ? Choice{LUPP_VARIANT_LANES, 16, 0} : c;
+    return bucket == 1 && n >= 9 && n <= 16 ? Choice{LUPP_VARIANT_LANES, 8, 4} : c;
+}
+
 void ctx_copy_settings(lupp_ctx *dst, const lupp_ctx *src)
 {
     dst->forced_variant = src->forced_variant;
@@ -267,10 +281,12 @@ int lupp_batched_solve(lupp_ctx *ctx, int n, int64_t batch, int layout, double *
     Choice c = ctx->table[n][layout][bucket_of(batch)];
     if (ctx->forced_variant != LUPP_VARIANT_AUTO) {
         c = Choice{ctx->forced_variant, ctx->forced_lanes, ctx->forced_wpb};
-    } else if (ctx->tile == 0 && !ctx->chosen[n][layout][bucket_of(batch)]) {
+    } else if (!ctx->chosen[n][layout][bucket_of(batch)]) {
         /* only where its address range holds too: strides beyond it keep the
          * table's entry */
-        const Choice r = auto_choice(n, layout, bucket_of(batch), (flags & LUPP_KEEP_A) == 0, c);
+        const Choice r = ctx->tile > 0
+                             ? tiled_choice(n, layout, bucket_of(batch), c)
+                             : auto_choice(n, layout, bucket_of(batch), (flags & LUPP_KEEP_A) == 0, c);
         if (fits_offsets(n, batch, layout, r.variant, r.lanes, strideA, strideB)) c = r;
     }
     LaunchFn fn = pick(n, c);

@@ -139,6 +139,17 @@ def test_interleaved_by_8_systems(L, ctx, n, lanes, batch):
             assert_bits(ref, *got[:4], b, **({"A": A} if keep else {}))
 
 
+@pytest.mark.parametrize("n,batch,soa", [(9, SMALL_BATCH, False), (16, SMALL_BATCH + 1, False),
+                                         (21, 300, True), (22, 300, True), (32, 37, True)])
+def test_tile_local_entries(L, n, batch, soa):
+    """Tile-local pivoting on the dispatcher's own entries, at their edges."""
+    ctx = L.Context(0)
+    A, b, _ = systems(n, batch, seed=8100 + n)
+    ref = oracle.gesv_batch_tiled(A, b, 4, 1e-10, threads=8)
+    assert L.lupp_set_pivoting(ctx, 4, 1e-10) == 0
+    assert_bits(ref, *gpu_solve(L, ctx, A, b, L.LUPP_SOA if soa else L.LUPP_AOS)[:4], b)
+
+
 def test_caller_chosen_entries_hold(L):
     """An entry the caller set serves solve-only calls too."""
     ctx = L.Context(0)
