@@ -123,7 +123,7 @@ def cpu_model() -> str:
 
 def cpu_oracle_baseline(host, sizes, newton=True, runs=10):
     """The CPU oracle as it stands, timed on this host: every core this
-    process may use (the pool's share, at most 16) and one core; one warm-up
+    process may use (at most 16) and one core; one warm-up
     then `runs` timed runs, median. Bounded samples: the first systems of the
     sweep's inputs per n, and the first points of the Newton workload."""
     import oracle

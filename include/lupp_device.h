@@ -92,9 +92,10 @@ __device__ __forceinline__ void settle(V &x)
     asm volatile("" : "+v"(x));
 }
 
-/* Whether the batched lanes kernels fence the solver's per-step results,
- * and their pivot-row broadcast chunk: the fence is used where it buys a
- * wave per SIMD and the wave pays - 16 lanes per system from n = 27
+/* Whether the batched kernels of this solver (tile-local pivoting) fence its
+ * per-step results, and their pivot-row broadcast chunk: the fence is used
+ * where it buys a wave per SIMD and the wave pays. The figures are those of
+ * the same solver with textbook pivoting: 16 lanes per system from n = 27
  * (195 -> 168 VGPRs at n = 32: three waves) and n = 20..24 with 4-column
  * chunks (<= 128 VGPRs: four waves instead of three; 4-7% faster at 2^19
  * systems, while n = 17..19 lost 1-3%). Elsewhere it would only hold the

@@ -37,7 +37,9 @@
  * Measured (262144 systems of N(0, 1) entries, packed, strict mode, us, solution
  * only / with factors; the ds_bpermute form -> this one): n = 32: 1187 / 1264 ->
  * 850 / 932; n = 24: 703 / 704 -> 518 / 541 (16 lanes), 456 / 582 (8 lanes). At
- * n = 32 the vector units are busy 73% of the time, LDS half of it.
+ * n = 32 (solution only, 2^20 systems) the vector units are busy 58% of the
+ * time and LDS 54%; a wave spends 24% of its life waiting to issue an LDS
+ * instruction.
  *
  * LDS traffic decides the shape of the broadcast: a masked ds_write_b128 costs
  * 13.7 cycles of the CU's LDS whatever the number of active lanes, a

@@ -101,9 +101,9 @@ __device__ __forceinline__ void newton_block(const lupp_points &pts, const LawK 
     }
 }
 
-/* Occupancy: 7 unknowns fit 3 waves per SIMD without scratch (146 VGPRs; 4
- * waves would spill 52 bytes per lane); 13 unknowns take the whole register
- * file of one wave (VGPRs and AGPRs) and no scratch. */
+/* Occupancy: 7 unknowns fit 3 waves per SIMD without scratch (152 VGPRs);
+ * 13 unknowns take the register file of one wave (408 VGPRs and AGPRs, 432
+ * with the tangent) and no scratch. */
 template <int NU>
 constexpr int newton_waves_per_eu() { return NU == 7 ? 3 : 1; }
 
@@ -231,10 +231,9 @@ static void launch_newton_lanes(const lupp_points *pts, const LawK &P, double to
 
 /* Default mapping per law, measured on gfx950 (2^20 points of the benchmark
  * increments, mean 17.7 solves per point): one lane per point wins for both
- * laws - 7 unknowns: 1.33 ms against 4.5 ms (4 lanes) and 6.6 ms (8 lanes);
- * 13 unknowns: 7.6 ms, despite 512 VGPRs with some scratch and one wave per
- * SIMD, against 17.9 ms (8 lanes) and 23 ms (16 lanes, 247 VGPRs, two
- * waves). Every lane of a group repeats the law's common part (pow, sqrt,
+ * laws - 7 unknowns: 0.56 ms against 3.3 ms (4 lanes) and 3.6 ms (8 lanes);
+ * 13 unknowns: 2.8 ms, despite one wave per SIMD, against 12.4 ms (8 lanes)
+ * and 17.8 ms (16 lanes, 216 VGPRs, two waves). Every lane of a group repeats the law's common part (pow, sqrt,
  * divisions), and the lanes LU's pivot search and broadcasts cost more than
  * the occupancy they buy back. */
 int newton_default_lanes(int) { return 1; }
