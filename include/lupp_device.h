@@ -200,8 +200,10 @@ __device__ __forceinline__ void masked_swap(uint64_t m, double &x0, double &y0, 
  * v_max_f64, then, row by row, the lanes whose entry has magnitude M and which
  * no earlier row has served: two instructions per candidate where carrying the
  * value and row of a running best takes seven, and the lowest such row is
- * textbook pivoting's choice (for a column without NaN). The tile-local rule,
- * with its bounded first search, carries the running best.
+ * textbook pivoting's choice. A finite matrix may overflow into NaN on the way;
+ * the choice is then that of the left-to-right scan for a larger magnitude too:
+ * M leaves NaN out, and a row k that is NaN is not below M, so it stays. The
+ * tile-local rule, with its bounded first search, carries the running best.
  *
  * Interchange: the pivot row is data while register indices are not, so rows
  * k and i are exchanged in the lanes that chose i, for one candidate row i at
@@ -236,13 +238,8 @@ __device__ __forceinline__ int thread_getrf_solve(double (&a)[N][N], double (&b)
             /* kRecip: the reciprocal needs only the magnitude, so its latency
              * runs under the interchange (a zero pivot gives an unused infinity) */
             if constexpr (kRecip) rp = 1.0 / best;
-            zero = best == 0.0;
-            info = (zero && info == 0) ? k + 1 : info;
-            /* solve-only calls on systems that spill into AGPRs (the 13 x 13
-             * Newton steps): fenced, see settle */
-            if constexpr (!kFactors && N >= 10) settle(info);
             int p = k;
-            uint64_t open = ~__ballot(fabs(a[k][k]) == best);
+            uint64_t open = __ballot(fabs(a[k][k]) < best);
             static_for<k + 1, N>(LUPP_SF(ic) {
                 constexpr int i = decltype(ic)::value;
                 const uint64_t hit = __ballot(fabs(a[k][i]) == best) & open;
@@ -264,7 +261,13 @@ __device__ __forceinline__ int thread_getrf_solve(double (&a)[N][N], double (&b)
             });
             ipiv[k] = p + 1;
             pv = a[k][k];
-            if constexpr (kRecip) rp = __builtin_copysign(rp, pv);
+            zero = pv == 0.0;
+            info = (zero && info == 0) ? k + 1 : info;
+            /* solve-only calls on systems that spill into AGPRs (the 13 x 13
+             * Newton steps): fenced, see settle */
+            if constexpr (!kFactors && N >= 10) settle(info);
+            /* the sign of the pivot, and NaN if it is */
+            if constexpr (kRecip) rp = __builtin_amdgcn_div_fixup(rp, pv, 1.0);
         } else {
             /* the rows k .. k1-1 first, then, if needed, every row k .. N-1 */
             const int k1 = pivot_tile_end(k, N, tile);
