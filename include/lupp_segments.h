@@ -323,22 +323,44 @@ __device__ __forceinline__ int seg_getrf_solve(double (&a)[(N + T - 1) / T][N],
     });
 
     /* pivot of column k: hit[s] = the lanes whose slot s is the pivot row,
-     * taken out of the candidates; key: high words, M: their maximum */
-    auto search = [&](auto kc, int (&key)[K], int &M, uint64_t (&hit)[K]) __attribute__((always_inline)) {
+     * taken out of the candidates; key: high words, M: their maximum; big: the
+     * lanes where M is above HI */
+    auto search = [&](auto kc, int (&key)[K], int &M, uint64_t (&hit)[K], uint64_t &big) __attribute__((always_inline)) {
         constexpr int k = decltype(kc)::value;
-        int lm = -1;
+        int nhit;
+        auto largest = [&]() __attribute__((always_inline)) {
+            int lm = -1;
+            static_for<0, K>(LUPP_SF(sc) {
+                constexpr int s = decltype(sc)::value;
+                lm = s == 0 ? key[0] : max(lm, key[s]);
+            });
+            M = seg_max<T>(lm);
+            nhit = 0;
+            static_for<0, K>(LUPP_SF(sc) {
+                constexpr int s = decltype(sc)::value;
+                hit[s] = __ballot(key[s] == M);
+                nhit += __builtin_popcountll(hit[s]);
+            });
+            big = __ballot(M > HI);
+        };
         static_for<0, K>(LUPP_SF(sc) {
             constexpr int s = decltype(sc)::value;
             key[s] = in_mask(cand[s]) ? seg_hi_abs(a[s][k]) : -1;
-            lm = s == 0 ? key[0] : max(lm, key[s]);
         });
-        M = seg_max<T>(lm);
-        int nhit = 0;
-        static_for<0, K>(LUPP_SF(sc) {
-            constexpr int s = decltype(sc)::value;
-            hit[s] = __ballot(key[s] == M);
-            nhit += __builtin_popcountll(hit[s]);
-        });
+        largest();
+        /* A candidate is NaN (a finite matrix may overflow into one): as in a
+         * scan for a larger magnitude, it is the pivot if it is the row at
+         * position k and is passed over otherwise. */
+        if (__builtin_expect(big != 0, 0)) {
+            uint64_t nan = 0;
+            static_for<0, K>(LUPP_SF(sc) {
+                constexpr int s = decltype(sc)::value;
+                const bool is = in_mask(cand[s]) && a[s][k] != a[s][k];
+                nan |= __ballot(is);
+                key[s] = is ? (pos[s] == k ? 0x7fffffff : -1) : key[s];
+            });
+            if (nan != 0) largest();
+        }
         /* every segment has a candidate, so SPW hits are one per segment */
         if (__builtin_expect(nhit != SPW, 0)) {
             int lv[K], l = 0, pm = 0;
@@ -390,10 +412,10 @@ __device__ __forceinline__ int seg_getrf_solve(double (&a)[(N + T - 1) / T][N],
     };
     /* multipliers: a[s][k] = a[s][k] / pv, correctly rounded, in the lanes m[s];
      * the pivot rows keep the reciprocal for the back substitution */
-    auto scale = [&](auto kc, const int (&key)[K], int M, const uint64_t (&m)[K],
+    auto scale = [&](auto kc, const int (&key)[K], uint64_t big, const uint64_t (&m)[K],
                      const uint64_t (&hit)[K], double pv) __attribute__((always_inline)) {
         constexpr int k = decltype(kc)::value;
-        uint64_t bad = __ballot(M > HI);
+        uint64_t bad = big;
         static_for<0, K>(LUPP_SF(sc) {
             bad |= __ballot((unsigned)key[decltype(sc)::value] < (unsigned)LO);
         });
@@ -426,10 +448,10 @@ __device__ __forceinline__ int seg_getrf_solve(double (&a)[(N + T - 1) / T][N],
         constexpr std::integral_constant<int, k> k0{};
         constexpr std::integral_constant<int, k + 1> k1{};
         int key[K], M;
-        uint64_t h0[K], h1[K], m0[K], m1[K];
+        uint64_t h0[K], h1[K], m0[K], m1[K], big;
 
         /* step k: its pivot row's entries k and k + 1 go out at once */
-        search(k0, key, M, h0);
+        search(k0, key, M, h0, big);
         {
             double x = a[0][k], z = a[0][k + 1];
             int p = pos[0];
@@ -449,7 +471,7 @@ __device__ __forceinline__ int seg_getrf_solve(double (&a)[(N + T - 1) / T][N],
         place(k0, h0, ipl[k]);
         const uint64_t z0 = note_zero(k0, p0.x), n0 = ~z0;
         static_for<0, K>(LUPP_SF(sc) { m0[decltype(sc)::value] = cand[decltype(sc)::value] & n0; });
-        scale(k0, key, M, m0, h0, p0.x);
+        scale(k0, key, big, m0, h0, p0.x);
         static_for<0, K>(LUPP_SF(sc) {
             constexpr int s = decltype(sc)::value;
             const double u[1] = {p0.y};
@@ -458,7 +480,7 @@ __device__ __forceinline__ int seg_getrf_solve(double (&a)[(N + T - 1) / T][N],
 
         /* step k + 1: both pivot rows from column k on, row k + 1 with its
          * multiplier and without step k's update */
-        search(k1, key, M, h1);
+        search(k1, key, M, h1, big);
         seg_order();
         static_for<0, K>(LUPP_SF(sc) {
             constexpr int s = decltype(sc)::value;
@@ -516,7 +538,7 @@ __device__ __forceinline__ int seg_getrf_solve(double (&a)[(N + T - 1) / T][N],
         place(k1, h1, ipl[k + 1]);
         const uint64_t z1 = note_zero(k1, p1.y);
         static_for<0, K>(LUPP_SF(sc) { m1[decltype(sc)::value] = cand[decltype(sc)::value] & ~z1; });
-        scale(k1, key, M, m1, h1, p1.y);
+        scale(k1, key, big, m1, h1, p1.y);
         /* row k + 1 takes step k's update unless that pivot was zero */
         masked_msub<kFMA, 1>(n0, p1.x, y1, y0);
         static_for<0, K>(LUPP_SF(sc) {

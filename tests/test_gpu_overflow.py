@@ -51,3 +51,16 @@ def test_thread_solver(L, ctx, n):
         for layout in (L.LUPP_AOS, L.LUPP_SOA):
             got = gpu_solve(L, ctx, A, b, layout, L.LUPP_VARIANT_THREAD, 1, fma=fma)
             check(ref, *got[:4], b)
+
+
+@pytest.mark.parametrize("n", [2, 4, 5, 8, 9, 12, 13, 16, 17, 20, 24, 25, 32])
+def test_lanes_solver(L, ctx, n):
+    A, b = overflowing(n, 300, seed=9100 + n)
+    for fma in (False, True):
+        ref = oracle.gesv_batch_mode(A, b, fma=fma, threads=4)
+        for variant, lanes in variants(n):
+            if variant != L.LUPP_VARIANT_LANES:
+                continue
+            for layout in (L.LUPP_AOS, L.LUPP_SOA):
+                got = gpu_solve(L, ctx, A, b, layout, variant, lanes, fma=fma)
+                check(ref, *got[:4], b)
