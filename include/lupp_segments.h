@@ -111,22 +111,24 @@ __device__ __forceinline__ int seg_max(int v)
     return v;
 }
 
-/* m ? x : y per lane, by a wave mask (asm: the compiler would turn a chain of
- * selects between register-array elements into an indexed scratch access) */
-__device__ __forceinline__ int mask_select(uint64_t m, int x, int y)
+/* x, z, p = m ? (xs, zs, ps) : (x, z, p) per lane, by a wave mask (asm: the
+ * compiler would turn a chain of selects between register-array elements into
+ * an indexed scratch access). A vector instruction may read a mask that a
+ * vector compare has written only two wait states later, and the compiler's
+ * hazard pass does not look inside asm: hence the s_nop. */
+__device__ __forceinline__ void mask_select(uint64_t m, double &x, double xs, double &z, double zs,
+                                            int &p, int ps)
 {
-    int r;
-    asm("v_cndmask_b32_e64 %0, %1, %2, %3" : "=v"(r) : "v"(y), "v"(x), "s"(m));
-    return r;
-}
-
-__device__ __forceinline__ double mask_select(uint64_t m, double x, double y)
-{
-    const int2 u = __builtin_bit_cast(int2, x), v = __builtin_bit_cast(int2, y);
-    int2 r;
-    r.x = mask_select(m, u.x, v.x);
-    r.y = mask_select(m, u.y, v.y);
-    return __builtin_bit_cast(double, r);
+    int2 u = __builtin_bit_cast(int2, x), v = __builtin_bit_cast(int2, z);
+    const int2 us = __builtin_bit_cast(int2, xs), vs = __builtin_bit_cast(int2, zs);
+    asm("s_nop 1\n\t"
+        "v_cndmask_b32_e64 %0, %0, %5, %10\n\tv_cndmask_b32_e64 %1, %1, %6, %10\n\t"
+        "v_cndmask_b32_e64 %2, %2, %7, %10\n\tv_cndmask_b32_e64 %3, %3, %8, %10\n\t"
+        "v_cndmask_b32_e64 %4, %4, %9, %10"
+        : "+&v"(u.x), "+&v"(u.y), "+&v"(v.x), "+&v"(v.y), "+&v"(p)
+        : "v"(us.x), "v"(us.y), "v"(vs.x), "v"(vs.y), "v"(ps), "s"(m));
+    x = __builtin_bit_cast(double, u);
+    z = __builtin_bit_cast(double, v);
 }
 
 /* Masked blocks: the wave enters with every lane active, works in the lanes of
@@ -458,9 +460,7 @@ __device__ __forceinline__ int seg_getrf_solve(double (&a)[(N + T - 1) / T][N],
             uint64_t own = h0[0];
             static_for<1, K>(LUPP_SF(sc) {
                 constexpr int s = decltype(sc)::value;
-                x = mask_select(h0[s], a[s][k], x);
-                z = mask_select(h0[s], a[s][k + 1], z);
-                p = mask_select(h0[s], pos[s], p);
+                mask_select(h0[s], x, a[s][k], z, a[s][k + 1], p, pos[s]);
                 own |= h0[s];
             });
             masked_put2<k>(own, rp, x, z);
