@@ -30,9 +30,10 @@
  *   - Divisions by one pivot share its reciprocal (two Newton-Raphson steps
  *     from v_rcp_f64); the quotient is then corrected with its exact residual
  *     (Markstein's method, as in the correctly rounded division the compiler
- *     emits, whose scaling steps do nothing in the range checked for). A wave
- *     with a pivot or numerator outside 2^-400 .. 2^400 (zeros included)
- *     takes true divisions instead.
+ *     emits, whose scaling steps do nothing in the range checked for). A zero
+ *     numerator has the exact quotient q = +-0 and residual 0. A wave with
+ *     another pivot or numerator outside 2^-400 .. 2^400 takes true divisions
+ *     instead.
  *
  * Measured (262144 systems of N(0, 1) entries, packed, strict mode, us, solution
  * only / with factors; the ds_bpermute form -> this one): n = 32: 1187 / 1264 ->
@@ -54,7 +55,7 @@ namespace lupp {
 
 /* LDS of one segment, in doubles: two pivot rows of kRow entries (n columns
  * and the right-hand side; even, so that pairs are 16-byte aligned), then
- * n + 1 int32 positions (the last one a sink). The stride is an odd number of
+ * the n int32 positions (with room to spare). The stride is an odd number of
  * 16-byte units: the segments of a wave then read from different banks. */
 template <int N>
 struct seg_lds {
@@ -325,44 +326,30 @@ __device__ __forceinline__ int seg_getrf_solve(double (&a)[(N + T - 1) / T][N],
     });
 
     /* pivot of column k: hit[s] = the lanes whose slot s is the pivot row,
-     * taken out of the candidates; key: high words, M: their maximum; big: the
-     * lanes where M is above HI */
-    auto search = [&](auto kc, int (&key)[K], int &M, uint64_t (&hit)[K], uint64_t &big) __attribute__((always_inline)) {
+     * taken out of the candidates; key: high words, M: their maximum. A NaN (a
+     * finite matrix may overflow into one) has the largest key and is found
+     * first; with has_nan it is the pivot if it is the row at position k and
+     * passed over otherwise, as in a scan for a larger magnitude. */
+    auto search = [&](auto kc, int (&key)[K], int &M, uint64_t (&hit)[K], auto has_nan) __attribute__((always_inline)) {
         constexpr int k = decltype(kc)::value;
-        int nhit;
-        auto largest = [&]() __attribute__((always_inline)) {
-            int lm = -1;
-            static_for<0, K>(LUPP_SF(sc) {
-                constexpr int s = decltype(sc)::value;
-                lm = s == 0 ? key[0] : max(lm, key[s]);
-            });
-            M = seg_max<T>(lm);
-            nhit = 0;
-            static_for<0, K>(LUPP_SF(sc) {
-                constexpr int s = decltype(sc)::value;
-                hit[s] = __ballot(key[s] == M);
-                nhit += __builtin_popcountll(hit[s]);
-            });
-            big = __ballot(M > HI);
-        };
+        int lm = -1;
         static_for<0, K>(LUPP_SF(sc) {
             constexpr int s = decltype(sc)::value;
-            key[s] = in_mask(cand[s]) ? seg_hi_abs(a[s][k]) : -1;
+            int c = seg_hi_abs(a[s][k]);
+            if constexpr (decltype(has_nan)::value) {
+                const bool is = a[s][k] != a[s][k];
+                c = is ? (pos[s] == k ? 0x7fffffff : -1) : c;
+            }
+            key[s] = in_mask(cand[s]) ? c : -1;
+            lm = s == 0 ? key[0] : max(lm, key[s]);
         });
-        largest();
-        /* A candidate is NaN (a finite matrix may overflow into one): as in a
-         * scan for a larger magnitude, it is the pivot if it is the row at
-         * position k and is passed over otherwise. */
-        if (__builtin_expect(big != 0, 0)) {
-            uint64_t nan = 0;
-            static_for<0, K>(LUPP_SF(sc) {
-                constexpr int s = decltype(sc)::value;
-                const bool is = in_mask(cand[s]) && a[s][k] != a[s][k];
-                nan |= __ballot(is);
-                key[s] = is ? (pos[s] == k ? 0x7fffffff : -1) : key[s];
-            });
-            if (nan != 0) largest();
-        }
+        M = seg_max<T>(lm);
+        int nhit = 0;
+        static_for<0, K>(LUPP_SF(sc) {
+            constexpr int s = decltype(sc)::value;
+            hit[s] = __ballot(key[s] == M);
+            nhit += __builtin_popcountll(hit[s]);
+        });
         /* every segment has a candidate, so SPW hits are one per segment */
         if (__builtin_expect(nhit != SPW, 0)) {
             int lv[K], l = 0, pm = 0;
@@ -400,10 +387,25 @@ __device__ __forceinline__ int seg_getrf_solve(double (&a)[(N + T - 1) / T][N],
             settle(pos[s]);
         });
     };
-    auto note_zero = [&](auto kc, double pv) __attribute__((always_inline)) -> uint64_t {
+    /* takes back search and place of step k */
+    auto unplace = [&](auto kc, const uint64_t (&hit)[K], int q) __attribute__((always_inline)) {
         constexpr int k = decltype(kc)::value;
-        const uint64_t z = __ballot(pv == 0.0);
-        if (__builtin_expect(z != 0, 0)) info = (pv == 0.0 && info == 0) ? k + 1 : info;
+        static_for<0, K>(LUPP_SF(sc) {
+            constexpr int s = decltype(sc)::value;
+            pos[s] = in_mask(hit[s]) ? q : (pos[s] == q ? k : pos[s]);
+            cand[s] |= hit[s];
+        });
+    };
+    /* the lanes whose pivot pv (as found, a NaN before any number) is zero;
+     * again(): takes the step back, searches with has_nan and does it anew */
+    auto check_pivot = [&](auto kc, const double &pv, auto again) __attribute__((always_inline)) -> uint64_t {
+        constexpr int k = decltype(kc)::value;
+        uint64_t z = __ballot(__builtin_amdgcn_class(pv, 0x63)); /* zeros and NaN */
+        if (__builtin_expect(z != 0, 0)) {
+            if (__ballot(pv != pv) != 0) again();
+            z = __ballot(pv == 0.0);
+            info = (pv == 0.0 && info == 0) ? k + 1 : info;
+        }
         settle(info);
         return z;
     };
@@ -414,35 +416,50 @@ __device__ __forceinline__ int seg_getrf_solve(double (&a)[(N + T - 1) / T][N],
     };
     /* multipliers: a[s][k] = a[s][k] / pv, correctly rounded, in the lanes m[s];
      * the pivot rows keep the reciprocal for the back substitution */
-    auto scale = [&](auto kc, const int (&key)[K], uint64_t big, const uint64_t (&m)[K],
+    auto scale = [&](auto kc, const int (&key)[K], int M, const uint64_t (&m)[K],
                      const uint64_t (&hit)[K], double pv) __attribute__((always_inline)) {
         constexpr int k = decltype(kc)::value;
+        const uint64_t big = __ballot(M > HI);
         uint64_t bad = big;
         static_for<0, K>(LUPP_SF(sc) {
             bad |= __ballot((unsigned)key[decltype(sc)::value] < (unsigned)LO);
         });
-        odd |= bad;
-        double y = reciprocal(pv), q[K], e[K];
+        double y = reciprocal(pv);
         static_for<0, K>(LUPP_SF(sc) { masked_mov(hit[decltype(sc)::value], ry[decltype(sc)::value], y); });
         if (__builtin_expect(bad == 0, 1)) {
+            double q[K], e[K];
             static_for<0, K>(LUPP_SF(sc) {
                 constexpr int s = decltype(sc)::value;
                 q[s] = a[s][k] * y;
                 e[s] = __builtin_fma(-pv, q[s], a[s][k]);
             });
-        } else {
             static_for<0, K>(LUPP_SF(sc) {
                 constexpr int s = decltype(sc)::value;
-                q[s] = a[s][k] / pv;
-                settle(q[s]); /* one division at a time */
-                e[s] = __builtin_copysign(0.0, q[s]); /* fma(e, 1, q) == q, signed zeros too */
+                masked_fma(m[s], a[s][k], e[s], y, q[s]);
             });
-            y = 1.0;
+        } else {
+            /* zeros, the usual case, are none of the values out of range */
+            bad = big;
+            static_for<0, K>(LUPP_SF(sc) {
+                constexpr int s = decltype(sc)::value;
+                bad |= __ballot(((unsigned)key[s] < (unsigned)LO) & (a[s][k] != 0.0));
+            });
+            if (bad == 0) {
+                /* q is the zero of the quotient's sign; a as the residual keeps it so */
+                settle(y);
+                static_for<0, K>(LUPP_SF(sc) {
+                    constexpr int s = decltype(sc)::value;
+                    const double q = a[s][k] * y, e = __builtin_fma(-pv, q, a[s][k]);
+                    masked_fma(m[s], a[s][k], a[s][k] == 0.0 ? a[s][k] : e, y, q);
+                });
+            } else {
+                odd |= bad;
+                static_for<0, K>(LUPP_SF(sc) {
+                    constexpr int s = decltype(sc)::value;
+                    masked_mov(m[s], a[s][k], a[s][k] / pv); /* one division at a time */
+                });
+            }
         }
-        static_for<0, K>(LUPP_SF(sc) {
-            constexpr int s = decltype(sc)::value;
-            masked_fma(m[s], a[s][k], e[s], y, q[s]);
-        });
     };
 
     static_for<0, N / 2>(LUPP_SF(kkc) {
@@ -450,11 +467,12 @@ __device__ __forceinline__ int seg_getrf_solve(double (&a)[(N + T - 1) / T][N],
         constexpr std::integral_constant<int, k> k0{};
         constexpr std::integral_constant<int, k + 1> k1{};
         int key[K], M;
-        uint64_t h0[K], h1[K], m0[K], m1[K], big;
+        uint64_t h0[K], h1[K], m0[K], m1[K];
 
         /* step k: its pivot row's entries k and k + 1 go out at once */
-        search(k0, key, M, h0, big);
-        {
+        seg_pair p0;
+        auto first = [&](auto has_nan) __attribute__((always_inline)) {
+            search(k0, key, M, h0, has_nan);
             double x = a[0][k], z = a[0][k + 1];
             int p = pos[0];
             uint64_t own = h0[0];
@@ -465,13 +483,19 @@ __device__ __forceinline__ int seg_getrf_solve(double (&a)[(N + T - 1) / T][N],
             });
             masked_put2<k>(own, rp, x, z);
             masked_put_i32<IP + 4 * k>(own, rp, p);
-        }
-        seg_order();
-        const seg_pair p0 = *reinterpret_cast<const seg_pair *>(rec + k);
+            seg_order();
+            p0 = *reinterpret_cast<const seg_pair *>(rec + k);
+        };
+        first(std::false_type{});
         place(k0, h0, ipl[k]);
-        const uint64_t z0 = note_zero(k0, p0.x), n0 = ~z0;
+        const uint64_t z0 = check_pivot(k0, p0.x, [&]() __attribute__((always_inline)) {
+            unplace(k0, h0, ipl[k]);
+            first(std::true_type{});
+            place(k0, h0, ipl[k]);
+        });
+        const uint64_t n0 = ~z0;
         static_for<0, K>(LUPP_SF(sc) { m0[decltype(sc)::value] = cand[decltype(sc)::value] & n0; });
-        scale(k0, key, big, m0, h0, p0.x);
+        scale(k0, key, M, m0, h0, p0.x);
         static_for<0, K>(LUPP_SF(sc) {
             constexpr int s = decltype(sc)::value;
             const double u[1] = {p0.y};
@@ -480,44 +504,6 @@ __device__ __forceinline__ int seg_getrf_solve(double (&a)[(N + T - 1) / T][N],
 
         /* step k + 1: both pivot rows from column k on, row k + 1 with its
          * multiplier and without step k's update */
-        search(k1, key, M, h1, big);
-        seg_order();
-        static_for<0, K>(LUPP_SF(sc) {
-            constexpr int s = decltype(sc)::value;
-            const unsigned r = in_mask(h1[s]) ? rp + RS * 8 : rp;
-            const uint64_t m = h0[s] | h1[s];
-            masked_put_i32<IP + 4 * (k + 1)>(h1[s], rp, pos[s]);
-            auto val = [&](auto jc) __attribute__((always_inline)) -> double {
-                constexpr int c = decltype(jc)::value;
-                if constexpr (c < N) return a[s][c];
-                else return b[s];
-            };
-            constexpr int cols = N + 1 - k, full = cols / 8 * 8;
-            static_for<0, cols / 8>(LUPP_SF(pc) {
-                constexpr int j = k + 8 * decltype(pc)::value;
-                masked_put8<j>(m, r, val(std::integral_constant<int, j>{}), val(std::integral_constant<int, j + 1>{}),
-                               val(std::integral_constant<int, j + 2>{}), val(std::integral_constant<int, j + 3>{}),
-                               val(std::integral_constant<int, j + 4>{}), val(std::integral_constant<int, j + 5>{}),
-                               val(std::integral_constant<int, j + 6>{}), val(std::integral_constant<int, j + 7>{}));
-            });
-            static_for<0, (cols - full + 3) / 4>(LUPP_SF(pc) {
-                constexpr int j = k + full + 4 * decltype(pc)::value;
-                const double x = val(std::integral_constant<int, j>{});
-                if constexpr (j + 3 <= N) {
-                    masked_put4<j>(m, r, x, val(std::integral_constant<int, j + 1>{}),
-                                   val(std::integral_constant<int, j + 2>{}),
-                                   val(std::integral_constant<int, j + 3>{}));
-                } else {
-                    if constexpr (j + 1 <= N) masked_put2<j>(m, r, x, val(std::integral_constant<int, j + 1>{}));
-                    else masked_put1<j>(m, r, x);
-                    if constexpr (j + 2 <= N) masked_put1<j + 2>(m, r, val(std::integral_constant<int, j + 2>{}));
-                }
-            });
-        });
-        seg_order();
-        const seg_pair p1 = *reinterpret_cast<const seg_pair *>(rec + RS + k); /* multiplier, pivot */
-        const double y0[1] = {rec[N]};
-        double y1[1] = {rec[RS + N]};
         constexpr int NC = (N - k - 2 + CH - 1) / CH;
         double u0[2][CH + 1], u1[2][CH + 1];
         auto fetch = [&](auto cc) __attribute__((always_inline)) {
@@ -534,11 +520,58 @@ __device__ __forceinline__ int seg_getrf_solve(double (&a)[(N + T - 1) / T][N],
                 u1[c & 1][j + 1 - j0] = w.y;
             });
         };
-        if constexpr (PF) fetch(std::integral_constant<int, 0>{});
+        seg_pair p1; /* multiplier, pivot */
+        double y0[1], y1[1];
+        auto second = [&](auto has_nan) __attribute__((always_inline)) {
+            search(k1, key, M, h1, has_nan);
+            seg_order();
+            static_for<0, K>(LUPP_SF(sc) {
+                constexpr int s = decltype(sc)::value;
+                const unsigned r = in_mask(h1[s]) ? rp + RS * 8 : rp;
+                const uint64_t m = h0[s] | h1[s];
+                masked_put_i32<IP + 4 * (k + 1)>(h1[s], rp, pos[s]);
+                auto val = [&](auto jc) __attribute__((always_inline)) -> double {
+                    constexpr int c = decltype(jc)::value;
+                    if constexpr (c < N) return a[s][c];
+                    else return b[s];
+                };
+                constexpr int cols = N + 1 - k, full = cols / 8 * 8;
+                static_for<0, cols / 8>(LUPP_SF(pc) {
+                    constexpr int j = k + 8 * decltype(pc)::value;
+                    masked_put8<j>(m, r, val(std::integral_constant<int, j>{}), val(std::integral_constant<int, j + 1>{}),
+                                   val(std::integral_constant<int, j + 2>{}), val(std::integral_constant<int, j + 3>{}),
+                                   val(std::integral_constant<int, j + 4>{}), val(std::integral_constant<int, j + 5>{}),
+                                   val(std::integral_constant<int, j + 6>{}), val(std::integral_constant<int, j + 7>{}));
+                });
+                static_for<0, (cols - full + 3) / 4>(LUPP_SF(pc) {
+                    constexpr int j = k + full + 4 * decltype(pc)::value;
+                    const double x = val(std::integral_constant<int, j>{});
+                    if constexpr (j + 3 <= N) {
+                        masked_put4<j>(m, r, x, val(std::integral_constant<int, j + 1>{}),
+                                       val(std::integral_constant<int, j + 2>{}),
+                                       val(std::integral_constant<int, j + 3>{}));
+                    } else {
+                        if constexpr (j + 1 <= N) masked_put2<j>(m, r, x, val(std::integral_constant<int, j + 1>{}));
+                        else masked_put1<j>(m, r, x);
+                        if constexpr (j + 2 <= N) masked_put1<j + 2>(m, r, val(std::integral_constant<int, j + 2>{}));
+                    }
+                });
+            });
+            seg_order();
+            p1 = *reinterpret_cast<const seg_pair *>(rec + RS + k);
+            y0[0] = rec[N];
+            y1[0] = rec[RS + N];
+            if constexpr (PF) fetch(std::integral_constant<int, 0>{});
+        };
+        second(std::false_type{});
         place(k1, h1, ipl[k + 1]);
-        const uint64_t z1 = note_zero(k1, p1.y);
+        const uint64_t z1 = check_pivot(k1, p1.y, [&]() __attribute__((always_inline)) {
+            unplace(k1, h1, ipl[k + 1]);
+            second(std::true_type{});
+            place(k1, h1, ipl[k + 1]);
+        });
         static_for<0, K>(LUPP_SF(sc) { m1[decltype(sc)::value] = cand[decltype(sc)::value] & ~z1; });
-        scale(k1, key, big, m1, h1, p1.y);
+        scale(k1, key, M, m1, h1, p1.y);
         /* row k + 1 takes step k's update unless that pivot was zero */
         masked_msub<kFMA, 1>(n0, p1.x, y1, y0);
         static_for<0, K>(LUPP_SF(sc) {
@@ -570,9 +603,9 @@ __device__ __forceinline__ int seg_getrf_solve(double (&a)[(N + T - 1) / T][N],
         });
         seg_order();
         const double pv = rec[k];
-        note_zero(std::integral_constant<int, k>{}, pv);
+        info = (pv == 0.0 && info == 0) ? N : info;
         const int h = seg_hi_abs(pv);
-        odd |= __ballot(h < LO || h > HI);
+        odd |= __ballot((h < LO || h > HI) && pv != 0.0);
         const double y = reciprocal(pv);
         static_for<0, K>(LUPP_SF(sc) { masked_mov(cand[decltype(sc)::value], ry[decltype(sc)::value], y); });
     }
@@ -583,9 +616,9 @@ __device__ __forceinline__ int seg_getrf_solve(double (&a)[(N + T - 1) / T][N],
 
     /* Back substitution, column j descending: the row at position j divides,
      * its x_j goes to rec[j], the rows above eliminate it. Divisions take the
-     * kept reciprocals; they are exact while every pivot (checked: odd) and
-     * every x_j (checked afterwards, so also every numerator) is in range. A
-     * wave where one is not (an exactly zero x_j among them) substitutes again
+     * kept reciprocals; they are exact while every pivot (checked: odd) is in
+     * range and every x_j (checked afterwards, so also every numerator) is in
+     * range or has the numerator +0. A wave where one is not substitutes again
      * from the saved right-hand side with true divisions. */
     if (__ballot(info == 0) != 0) {
         double b0[K];
@@ -623,11 +656,22 @@ __device__ __forceinline__ int seg_getrf_solve(double (&a)[(N + T - 1) / T][N],
         uint64_t redo = odd;
         if (redo == 0) {
             subst(std::false_type{});
+            /* b[s] is the row's numerator now: +0 gives the zero of the right
+             * sign, -0 may not */
+            uint64_t out[K];
             static_for<0, K>(LUPP_SF(sc) {
                 constexpr int s = decltype(sc)::value;
                 const int h = seg_hi_abs(rec[pos[s] >= 0 ? pos[s] : 0]);
-                redo |= __ballot(info == 0 && (h < (1023 - 300) << 20 || h > (1023 + 300) << 20));
+                out[s] = __ballot(info == 0 && (h < (1023 - 300) << 20 || h > (1023 + 300) << 20));
+                redo |= out[s];
             });
+            if (__builtin_expect(redo != 0, 0)) {
+                redo = 0;
+                static_for<0, K>(LUPP_SF(sc) {
+                    constexpr int s = decltype(sc)::value;
+                    redo |= out[s] & __ballot(pos[s] >= 0 && __builtin_bit_cast(uint64_t, b[s]) != 0);
+                });
+            }
             static_for<0, K>(LUPP_SF(sc) { b[decltype(sc)::value] = b0[decltype(sc)::value]; });
         }
         if (__builtin_expect(redo != 0, 0)) subst(std::true_type{});

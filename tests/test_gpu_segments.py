@@ -159,3 +159,47 @@ def test_caller_chosen_entries_hold(L):
     A, b, _ = systems(n, batch, seed=7800)
     ref = oracle.gesv_batch(A, b, threads=8)
     assert_bits(ref, *gpu_solve(L, ctx, A, b, L.LUPP_AOS, keep_a=True)[:4], b, A=A)
+
+
+def zero_systems(n, seed):
+    """Finite, well-scaled matrices and right-hand sides with exact zeros of
+    both signs, and what must not be taken for one: numerators below 2^-1042,
+    whose high word is zero, and solutions that underflow."""
+    r = np.random.default_rng(seed)
+    A, b, _ = systems(n, 24, seed=seed)
+    i = np.arange(n)
+    d = np.abs(i[:, None] - i[None, :])
+    band = np.where(d <= 2, A[:4], 0.0)
+    block = np.where(i[:, None] // 4 == i[None, :] // 4, A[4:8], -0.0)
+    half = np.where(r.random((4, n, n)) < 0.5, A[8:12], r.choice([0.0, -0.0], (4, n, n)))
+    tiny = np.where((r.random((4, n, n)) < 0.6) & (d > 0), r.choice([2.0 ** -1060, -0.0], (4, n, n)), A[12:16])
+    out = [(band, b[:4]), (block, b[4:8]), (half, b[8:12]), (tiny, b[12:16])]
+    for rhs in (0.0, -0.0, 2.0 ** -1060):
+        out.append((A[16:20], np.full((4, n), rhs)))
+    e = np.zeros((4, n))
+    e[np.arange(4), np.arange(4) % n] = 1.0
+    m = np.where(r.random((4, n)) < 0.5, b[16:20], r.choice([0.0, -0.0], (4, n)))
+    out += [(A[16:20], e), (A[16:20], m), (band, e), (band, m), (np.triu(A[20:24]), m),
+            (np.ldexp(A[20:24], 390), np.ldexp(b[20:24], -1000)), (half, -e)]
+    return np.concatenate([o[0] for o in out]), np.concatenate([o[1] for o in out])
+
+
+@pytest.mark.parametrize("n", [2, 3, 5, 8, 9, 12, 13, 16, 17, 24, 25, 32])
+@pytest.mark.parametrize("mixed", [True, False])
+def test_zeros(L, ctx, n, mixed):
+    """Zeros alone in a wave, and beside values that need true divisions."""
+    A, b = zero_systems(n, seed=8300 + n)
+    if mixed:
+        at = np.random.default_rng(n).permutation(len(A))
+        A, b = A[at], b[at]
+    else:
+        A, b = np.repeat(A, 32, axis=0), np.repeat(b, 32, axis=0)
+    for fma in (False, True):
+        ref = oracle.gesv_batch_mode(A, b, fma=fma, threads=8)
+        for variant, lanes in variants(n):
+            if variant != 2:
+                continue
+            for layout in (L.LUPP_AOS, L.LUPP_SOA):
+                got = gpu_solve(L, ctx, A, b, layout, variant, lanes, fma=fma)
+                assert got[4]
+                assert_bits(ref, *got[:4], b)
