@@ -247,15 +247,24 @@ int lupp_force_variant(lupp_ctx *ctx, int variant, int lanes, int wpb);
 /* Set / read the dispatch-table entry used for size n, layout and batches of
  * the size class of `batch` (below 32768 systems, or from 32768 on). The
  * table starts from the entries the autotuner measured on gfx950 with the
- * factors written. Until the caller sets or autotunes an entry, batches from
- * 32768 systems on may run a kernel that measured faster without the factors
- * (LUPP_KEEP_A) or in the interleaved layout, among them widths that cannot be
- * forced, and tile-local pivoting may run entries of its own; results do not
- * depend on it. */
+ * factors written. Until the caller sets an entry, batches from 32768 systems
+ * on may run a kernel that measured faster without the factors (LUPP_KEEP_A)
+ * or in the interleaved layout, among them widths that cannot be forced, and
+ * tile-local pivoting may run entries of its own; results do not depend on it.
+ * An entry that lupp_autotune measured serves the calls it timed (see there).
+ * lupp_get_solve_kernel says what a call runs. */
 int lupp_set_dispatch(lupp_ctx *ctx, int n, int layout, int64_t batch, int variant, int lanes,
                       int wpb);
 int lupp_get_dispatch(lupp_ctx *ctx, int n, int layout, int64_t batch, int *variant, int *lanes,
                       int *wpb);
+
+/* The kernel that lupp_batched_solve runs for size n, layout, batch and flags
+ * on packed strides under the context's settings: LUPP_VARIANT_THREAD, or
+ * LUPP_VARIANT_LANES with its lane count (widths that cannot be forced among
+ * them), and waves per workgroup as in lupp_force_variant. 0, or -i for a bad
+ * argument i, LUPP_E_UNSUPPORTED where the call would be. */
+int lupp_get_solve_kernel(lupp_ctx *ctx, int n, int layout, int64_t batch, unsigned flags,
+                          int *variant, int *lanes, int *wpb);
 
 /* Autotune the dispatch entry for size n, layout and the size class of batch
  * (Section 4.1: launch
@@ -264,7 +273,11 @@ int lupp_get_dispatch(lupp_ctx *ctx, int n, int layout, int64_t batch, int *vari
  * (A and b are only read), keep the fastest in the context's dispatch table,
  * and report it. Synchronous: allocates and frees its own device workspace
  * (the size of A, b, ipiv and info) and waits for `stream`. reps >= 1 timed
- * launches per candidate after one warm-up; the median is compared. */
+ * launches per candidate after one warm-up; the median is compared. The calls
+ * timed write the factors, under the context's pivoting: such calls run the
+ * entry from then on, unless a width that cannot be forced, timed beside the
+ * candidates, is faster; solve-only calls (LUPP_KEEP_A) were not timed and
+ * keep the rules they had. */
 int lupp_autotune(lupp_ctx *ctx, int n, int64_t batch, int layout, const double *A, int64_t lda,
                   int64_t strideA, const double *b, int64_t strideB, int reps, int *variant,
                   int *lanes, int *wpb, float *ms, void *stream);

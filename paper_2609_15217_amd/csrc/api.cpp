@@ -5,22 +5,9 @@
 #include <cstring>
 #include <new>
 
+#include "dispatch_rules.h"
 #include "internal.h"
 #include "serving.h"
-
-namespace lupp {
-
-struct Choice {
-    int variant;  /* LUPP_VARIANT_THREAD / LUPP_VARIANT_LANES / kVariantNarrow */
-    int lanes;
-    int wpb;
-};
-
-/* The lanes solver with half the lanes (twice the rows per lane) of the
- * variants lupp_force_variant names: chosen by auto_choice only. */
-constexpr int kVariantNarrow = 3;
-
-}  // namespace lupp
 
 struct lupp_ctx {
     int device;
@@ -28,7 +15,7 @@ struct lupp_ctx {
     int forced_lanes = 0;
     int forced_wpb = 0;
     lupp::Choice table[33][2][2]; /* [n][layout][batch bucket] */
-    bool chosen[33][2][2] = {};   /* entries the caller set or autotuned */
+    uint8_t binds[33][2][2] = {}; /* the calls each entry binds (EntryBinds) */
     lupp::RaggedWs *ragged_ws = nullptr; /* device workspace of the ragged path */
     lupp::BnWs *bn_ws = nullptr;         /* device workspace of the batched Newton */
     int newton_lanes[2] = {lupp::newton_default_lanes(LUPP_LAW_NORTON7),
@@ -84,47 +71,18 @@ static LaunchFn pick(int n, const Choice &c)
     return nullptr;
 }
 
-/* Refinement of a built-in table entry by what the table does not hold: large
- * batches that only solve (LUPP_KEEP_A). The table is tuned with the factors
- * written, where stores of whole lines decide and more lanes per system win;
- * without them instructions decide, and fewer lanes with more rows each spend
- * fewer per system. Measured at 2^20 systems (n <= 16) and 2^18 (above), us,
- * solve-only, table entry -> this one:
- *   AoS  n = 3: 30.7 -> 24.4 (thread); n = 8: 156 -> 136, n = 5: 86.8 -> 64.2
- *        (4 lanes); n = 12: 392 -> 289 (4 lanes, 3 rows each); n = 16: 667 ->
- *        618 (8 lanes against 16); n = 24: 555 -> 435 (8 lanes, 3 rows each);
- *        n = 32 at 2^20: 3538 -> 3425 (2 waves per workgroup against 4)
- *   SoA  n = 12: 466 -> 335 (4 lanes against the thread kernel, which wins up
- *        to n = 10: 225 against 247); n = 24: 654 -> 529
- * The interleaved layout stores whole lines with any segment width, so 8 lanes
- * also win there with the factors (n = 24: 767 -> 711; n = 17: 421 -> 353). */
-static Choice auto_choice(int n, int layout, int bucket, bool factors, const Choice &c)
+/* The kernel of a call with these settings: the forced variant, else the
+ * table's entry or its refinement - only where the refinement's address range
+ * holds too: strides beyond it keep the entry. */
+static Choice call_choice(const lupp_ctx *ctx, int n, int64_t batch, int layout, bool factors,
+                          int64_t sA, int64_t sB)
 {
-    if (bucket == 0) return c;
-    const bool aos = layout == LUPP_AOS;
-    if (n >= 17 && n <= 24 && (!aos || !factors)) return {kVariantNarrow, 8, 1};
-    if (factors) return c;
-    if (!aos) return (n == 11 || n == 12) ? Choice{kVariantNarrow, 4, 0} : c;
-    if (n == 2 || n == 3) return {LUPP_VARIANT_THREAD, 1, 1};
-    if (n >= 5 && n <= 8) return {LUPP_VARIANT_LANES, 4, 2};
-    if (n >= 9 && n <= 12) return {kVariantNarrow, 4, 2};
-    if (n >= 13 && n <= 16) return {LUPP_VARIANT_LANES, 8, 4};
-    if (n >= 27) return {LUPP_VARIANT_LANES, 16, 2};
-    return c;
-}
-
-/* Tile-local pivoting runs other kernels (kernels_lanes.h) than those the
- * table's entries were measured with. Packed batches of n = 9..16 are faster
- * with two rows per lane there (tile 4, 524288 systems, factors, us, table's
- * entry -> this: n = 9: 236 -> 212; n = 12: 371 -> 315; n = 16: 582 -> 487),
- * small interleaved ones from n = 22 on with 16 lanes (4096 systems: n = 28:
- * 40.5 -> 39.3; n = 32: 47.9 -> 47.0; n = 17 would lose, 22.9 -> 23.4). The
- * other entries measured within 3% of the best. */
-static Choice tiled_choice(int n, int layout, int bucket, const Choice &c)
-{
-    if (layout == LUPP_SOA)
-        return bucket == 0 && n >= 22 ? Choice{LUPP_VARIANT_LANES, 16, 0} : c;
-    return bucket == 1 && n >= 9 && n <= 16 ? Choice{LUPP_VARIANT_LANES, 8, 4} : c;
+    if (ctx->forced_variant != LUPP_VARIANT_AUTO)
+        return {ctx->forced_variant, ctx->forced_lanes, ctx->forced_wpb};
+    const int bk = bucket_of(batch);
+    const Choice c = ctx->table[n][layout][bk];
+    const Choice r = refined_choice(n, layout, bk, factors, ctx->tile > 0, ctx->binds[n][layout][bk], c);
+    return fits_offsets(n, batch, layout, r.variant, r.lanes, sA, sB) ? r : c;
 }
 
 void ctx_copy_settings(lupp_ctx *dst, const lupp_ctx *src)
@@ -133,7 +91,7 @@ void ctx_copy_settings(lupp_ctx *dst, const lupp_ctx *src)
     dst->forced_lanes = src->forced_lanes;
     dst->forced_wpb = src->forced_wpb;
     std::memcpy(dst->table, src->table, sizeof(dst->table));
-    std::memcpy(dst->chosen, src->chosen, sizeof(dst->chosen));
+    std::memcpy(dst->binds, src->binds, sizeof(dst->binds));
     dst->newton_lanes[0] = src->newton_lanes[0];
     dst->newton_lanes[1] = src->newton_lanes[1];
     dst->tile = src->tile;
@@ -230,7 +188,7 @@ int lupp_set_dispatch(lupp_ctx *ctx, int n, int layout, int64_t batch, int varia
     if (pick(n, c) == nullptr) return -6;
     if (wpb != 0 && wpb != 1 && wpb != 2 && wpb != 4) return -7;
     ctx->table[n][layout][bucket_of(batch)] = c;
-    ctx->chosen[n][layout][bucket_of(batch)] = true;
+    ctx->binds[n][layout][bucket_of(batch)] = kBindsAll;
     return 0;
 }
 
@@ -243,6 +201,24 @@ int lupp_get_dispatch(lupp_ctx *ctx, int n, int layout, int64_t batch, int *vari
     if (batch < 0) return -4;
     const Choice &c = ctx->table[n][layout][bucket_of(batch)];
     if (variant) *variant = c.variant;
+    if (lanes) *lanes = c.lanes;
+    if (wpb) *wpb = c.wpb;
+    return 0;
+}
+
+int lupp_get_solve_kernel(lupp_ctx *ctx, int n, int layout, int64_t batch, unsigned flags,
+                          int *variant, int *lanes, int *wpb)
+{
+    if (ctx == nullptr) return -1;
+    if (n < 1 || n > 32) return -2;
+    if (layout != LUPP_AOS && layout != LUPP_SOA) return -3;
+    if (batch < 0) return -4;
+    if ((flags & ~(LUPP_KEEP_A | LUPP_FMA)) != 0) return -5;
+    const bool aos = layout == LUPP_AOS;
+    const Choice c = call_choice(ctx, n, batch, layout, (flags & LUPP_KEEP_A) == 0,
+                                 aos ? n * n : batch, aos ? n : batch);
+    if (pick(n, c) == nullptr) return LUPP_E_UNSUPPORTED;
+    if (variant) *variant = c.variant == kVariantNarrow ? LUPP_VARIANT_LANES : c.variant;
     if (lanes) *lanes = c.lanes;
     if (wpb) *wpb = c.wpb;
     return 0;
@@ -278,17 +254,7 @@ int lupp_batched_solve(lupp_ctx *ctx, int n, int64_t batch, int layout, double *
 
     /* compiled instances: strict, FMA, strict with tile-local pivoting */
     if ((flags & LUPP_FMA) != 0 && ctx->tile > 0) return LUPP_E_UNSUPPORTED;
-    Choice c = ctx->table[n][layout][bucket_of(batch)];
-    if (ctx->forced_variant != LUPP_VARIANT_AUTO) {
-        c = Choice{ctx->forced_variant, ctx->forced_lanes, ctx->forced_wpb};
-    } else if (!ctx->chosen[n][layout][bucket_of(batch)]) {
-        /* only where its address range holds too: strides beyond it keep the
-         * table's entry */
-        const Choice r = ctx->tile > 0
-                             ? tiled_choice(n, layout, bucket_of(batch), c)
-                             : auto_choice(n, layout, bucket_of(batch), (flags & LUPP_KEEP_A) == 0, c);
-        if (fits_offsets(n, batch, layout, r.variant, r.lanes, strideA, strideB)) c = r;
-    }
+    Choice c = call_choice(ctx, n, batch, layout, (flags & LUPP_KEEP_A) == 0, strideA, strideB);
     LaunchFn fn = pick(n, c);
     if (fn == nullptr) return LUPP_E_UNSUPPORTED;
     if (!fits_offsets(n, batch, layout, c.variant, c.lanes, strideA, strideB)) {
@@ -466,37 +432,54 @@ int lupp_autotune(lupp_ctx *ctx, int n, int64_t batch, int layout, const double 
             cands[nc++] = {LUPP_VARIANT_LANES, widths[i], layout == LUPP_SOA ? 0 : w};
     }
     SolveArgs a{batch, wA, lda, strideA, wB, strideB, wP, wI, ctx->tile, ctx->thresh, 0};
-    for (int c = 0; c < nc && rc == 0; ++c) {
-        if (!fits_offsets(n, batch, layout, cands[c].variant, cands[c].lanes, strideA, strideB))
-            continue;
-        LaunchFn fn = pick(n, cands[c]);
+    /* median time of a kernel over the repetitions, in ms (first launch: warm-up) */
+    auto time_kernel = [&](const Choice &c, float &med) {
+        LaunchFn fn = pick(n, c);
         float t[64];
         const int r_total = reps + 1 < 64 ? reps + 1 : 64;
         for (int r = 0; r < r_total && rc == 0; ++r) {
             e = hipMemcpyAsync(wA, A, nA * 8, hipMemcpyDeviceToDevice, st);
             if (e == hipSuccess) e = hipMemcpyAsync(wB, b, nB * 8, hipMemcpyDeviceToDevice, st);
             if (e == hipSuccess) e = hipEventRecord(e0, st);
-            if (e == hipSuccess) e = fn(a, layout, true, cands[c].wpb, st);
+            if (e == hipSuccess) e = fn(a, layout, true, c.wpb, st);
             if (e == hipSuccess) e = hipEventRecord(e1, st);
             if (e == hipSuccess) e = hipEventSynchronize(e1);
             if (e == hipSuccess) e = hipEventElapsedTime(&t[r], e0, e1);
             if (e != hipSuccess) rc = hip_err(e);
         }
-        if (rc != 0) break;
-        /* median of the timed repetitions (the first launch is a warm-up) */
+        if (rc != 0) return;
         for (int i = 1; i < r_total; ++i)
             for (int j = i + 1; j < r_total; ++j)
                 if (t[j] < t[i]) { float x = t[i]; t[i] = t[j]; t[j] = x; }
-        const float med = t[1 + (r_total - 1) / 2];
-        if (med < best_ms) { best_ms = med; best = cands[c]; }
+        med = t[1 + (r_total - 1) / 2];
+    };
+    for (int c = 0; c < nc && rc == 0; ++c) {
+        if (!fits_offsets(n, batch, layout, cands[c].variant, cands[c].lanes, strideA, strideB))
+            continue;
+        float med = 3.0e38f;
+        time_kernel(cands[c], med);
+        if (rc == 0 && med < best_ms) { best_ms = med; best = cands[c]; }
     }
     if (rc == 0 && best.variant != 0) {
-        ctx->table[n][layout][bucket_of(batch)] = best;
-        ctx->chosen[n][layout][bucket_of(batch)] = true;
-        if (variant) *variant = best.variant;
-        if (lanes) *lanes = best.lanes;
-        if (wpb) *wpb = best.wpb;
-        if (ms) *ms = best_ms;
+        /* the entry binds the calls that were timed, unless the kernel that a
+         * call with the factors would otherwise run is faster still; solve-only
+         * calls were not timed */
+        const int bk = bucket_of(batch);
+        uint8_t binds = kBindsTiled;
+        const Choice r = refined_choice(n, layout, bk, true, false, 0, best);
+        float refined_ms = 3.0e38f;
+        if (ctx->tile == 0 && r.variant == kVariantNarrow &&
+            fits_offsets(n, batch, layout, r.variant, r.lanes, strideA, strideB))
+            time_kernel(r, refined_ms);
+        if (rc == 0 && ctx->tile == 0 && !(refined_ms < best_ms)) binds |= kBindsFactors;
+        if (rc == 0) {
+            ctx->table[n][layout][bk] = best;
+            ctx->binds[n][layout][bk] = binds;
+            if (variant) *variant = best.variant;
+            if (lanes) *lanes = best.lanes;
+            if (wpb) *wpb = best.wpb;
+            if (ms) *ms = best_ms;
+        }
     } else if (rc == 0) {
         rc = LUPP_E_UNSUPPORTED;
     }

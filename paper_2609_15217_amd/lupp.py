@@ -86,6 +86,10 @@ _lupp_set_dispatch = _sig("lupp_set_dispatch", ctypes.c_int,
 _lupp_get_dispatch = _sig("lupp_get_dispatch", ctypes.c_int,
                           [_P, ctypes.c_int, ctypes.c_int, _i64, ctypes.POINTER(ctypes.c_int),
                            ctypes.POINTER(ctypes.c_int), ctypes.POINTER(ctypes.c_int)])
+_lupp_get_solve_kernel = _sig("lupp_get_solve_kernel", ctypes.c_int,
+                              [_P, ctypes.c_int, ctypes.c_int, _i64, ctypes.c_uint,
+                               ctypes.POINTER(ctypes.c_int), ctypes.POINTER(ctypes.c_int),
+                               ctypes.POINTER(ctypes.c_int)])
 _lupp_variant_info = _sig("lupp_variant_info", ctypes.c_int,
                           [ctypes.c_int, ctypes.c_int, ctypes.c_int, ctypes.c_int, ctypes.c_int,
                            ctypes.POINTER(lupp_kernel_info)])
@@ -154,7 +158,7 @@ EXPORTED = ["lupp_create", "lupp_destroy", "lupp_batched_solve", "lupp_batched_s
             "lupp_get_newton_variant", "lupp_set_pivoting", "lupp_get_pivoting",
             "lupp_ragged_lanes_supported", "lupp_set_ragged_lanes", "lupp_get_ragged_lanes",
             "lupp_autotune_ragged", "lupp_batched_solve_ragged_noalloc",
-            "lupp_batched_solve_grouped"]
+            "lupp_batched_solve_grouped", "lupp_get_solve_kernel"]
 
 
 class LuppError(RuntimeError):
@@ -316,6 +320,14 @@ def lupp_get_dispatch(ctx: Context, n: int, layout: int, batch: int = 1 << 20):
     v, l, w = ctypes.c_int(), ctypes.c_int(), ctypes.c_int()
     _check(_lupp_get_dispatch(ctx.handle, n, layout, batch, ctypes.byref(v), ctypes.byref(l),
                               ctypes.byref(w)), "lupp_get_dispatch")
+    return v.value, l.value, w.value
+
+
+def lupp_get_solve_kernel(ctx: Context, n: int, layout: int, batch: int, flags: int = 0):
+    """(variant, lanes, wpb) of the kernel a packed lupp_batched_solve call runs."""
+    v, l, w = ctypes.c_int(), ctypes.c_int(), ctypes.c_int()
+    _check(_lupp_get_solve_kernel(ctx.handle, n, layout, batch, flags, ctypes.byref(v),
+                                  ctypes.byref(l), ctypes.byref(w)), "lupp_get_solve_kernel")
     return v.value, l.value, w.value
 
 
