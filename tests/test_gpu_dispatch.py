@@ -61,3 +61,13 @@ def test_forced_variant_is_reported(L):
     assert L.lupp_get_solve_kernel(ctx, 20, L.LUPP_AOS, LARGE, L.LUPP_KEEP_A) == (2, 32, 2)
     with pytest.raises(L.LuppError):
         L.lupp_get_solve_kernel(ctx, 8, L.LUPP_AOS, LARGE)  # no 32-lane kernel of this size
+
+
+@pytest.mark.parametrize("n,batch,kernel", [(5, 20000, (1, 1, 1)), (6, LARGE, (1, 1, 2)),
+                                            (7, LARGE, (1, 1, 2)), (13, LARGE, (2, 8, 0))])
+def test_interleaved_entries(L, n, batch, kernel):
+    """Entries that measured faster over their whole size class than the one
+    that won at the size the table was tuned at."""
+    ctx = L.Context(0)
+    for flags in (0, L.LUPP_KEEP_A):
+        assert L.lupp_get_solve_kernel(ctx, n, L.LUPP_SOA, batch, flags) == kernel
