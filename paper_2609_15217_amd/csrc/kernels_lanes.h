@@ -153,10 +153,11 @@ hipError_t launch_lanes(const SolveArgs &a, int layout, bool factors, int wpb, h
     }                                                                              \
     }
 
-/* The textbook-pivoting kernels alone (see narrow_launcher). */
+/* The textbook-pivoting kernels alone (see narrow_launcher); n = 9..11 run
+ * them in the packed layout only (auto_choice). */
 #define LUPP_NARROW_INSTANCE(N, T)                                                  \
     namespace lupp {                                                               \
-    LaunchFn narrow_fn_##N() { return launch_seg<N, T>; }                          \
+    LaunchFn narrow_fn_##N() { return launch_seg<N, T, (N > 11)>; }                \
     }
 
 #endif

@@ -2,8 +2,10 @@
  * interleaved (SoA) layout: the staging of kernels_lanes_soa.h (a workgroup
  * moves the matrices of 16 consecutive systems through LDS in whole 128-byte
  * lines) around the solver of lupp_segments.h. Measured against the
- * ds_bpermute solver in the same staging: see kernels_seg.h; one workgroup
- * holds 16/(64/T) waves, whose solver records reuse the staging tile.
+ * ds_bpermute solver in the same staging (200000 systems, solution only, us):
+ * n = 16 with 8 lanes 160 -> 129, n = 24 539 -> 391 (8 lanes against 16),
+ * n = 32 with 16 lanes 872 -> 737. One workgroup holds 16/(64/T) waves, whose
+ * solver records reuse the staging tile.
  * Other numbers of systems per workgroup: see seg_soa_systems (32) and
  * seg_soa_by_8. */
 #ifndef LUPP_KERNELS_SEG_SOA_H
@@ -265,14 +267,20 @@ bool seg_soa_by_8(const SolveArgs &a)
     return busiest(8) * 8 <= busiest(16) * 7;
 }
 
-template <int N, int T>
+/* kSoa: whether the interleaved kernels are built too */
+template <int N, int T, bool kSoa = true>
 hipError_t launch_seg(const SolveArgs &a, int layout, bool factors, int wpb, hipStream_t st)
 {
-    if constexpr (T >= 16)
-        if (layout == LUPP_SOA && seg_soa_by_8<T>(a)) return launch_seg_soa<N, T, 8>(a, factors, st);
-    if (layout == LUPP_SOA)
-        return factors ? launch_seg_soa<N, T, seg_soa_systems<N, T>(true)>(a, factors, st)
-                       : launch_seg_soa<N, T, seg_soa_systems<N, T>(false)>(a, factors, st);
+    if (layout == LUPP_SOA) {
+        if constexpr (kSoa) {
+            if constexpr (T >= 16)
+                if (seg_soa_by_8<T>(a)) return launch_seg_soa<N, T, 8>(a, factors, st);
+            return factors ? launch_seg_soa<N, T, seg_soa_systems<N, T>(true)>(a, factors, st)
+                           : launch_seg_soa<N, T, seg_soa_systems<N, T>(false)>(a, factors, st);
+        } else {
+            return hipErrorNotSupported;
+        }
+    }
     const int w = wpb > 0 ? wpb : 4;
     const int64_t per_block = (int64_t)w * (64 / T);
     const dim3 grid((unsigned)((a.batch + per_block - 1) / per_block));
