@@ -75,7 +75,7 @@ def log(msg: str):
 
 
 # the sources the standalone-solve kernels are compiled from, the dispatch
-# table that picks them and the compile flags: counters taken on other
+# table and rules that pick them and the compile flags: counters taken on other
 # sources do not describe the kernels this run launches
 KERNEL_SOURCES = ("include/lupp.h", "include/lupp_device.h", "include/lupp_segments.h",
                   "paper_2609_15217_amd/csrc/internal.h",
@@ -84,6 +84,7 @@ KERNEL_SOURCES = ("include/lupp.h", "include/lupp_device.h", "include/lupp_segme
                   "paper_2609_15217_amd/csrc/kernels_lanes_soa.h",
                   "paper_2609_15217_amd/csrc/kernels_seg.h",
                   "paper_2609_15217_amd/csrc/kernels_seg_soa.h",
+                  "paper_2609_15217_amd/csrc/dispatch_rules.h",
                   "paper_2609_15217_amd/dispatch_gfx950.json")
 
 
@@ -456,7 +457,7 @@ def main():
         n, lay = k
         gbs = bytes_per_system(n) * BATCH / (ms * 1e-3) / 1e9
         tfl = flops_per_system(n) * BATCH / (ms * 1e-3) / 1e12
-        v, lanes, wpb = L.lupp_get_dispatch(ctx, n, L.LUPP_SOA if lay == "soa" else L.LUPP_AOS, BATCH)
+        v, lanes, wpb = L.lupp_get_solve_kernel(ctx, n, L.LUPP_SOA if lay == "soa" else L.LUPP_AOS, BATCH)
         per_kernel.append({"n": n, "layout": lay, "ms": round(ms, 4),
                            "systems_per_s": round(BATCH / (ms * 1e-3)),
                            "GBps": round(gbs, 1), "hbm_frac": round(gbs / HBM_PEAK_GBS, 4),
