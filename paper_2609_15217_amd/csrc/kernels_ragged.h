@@ -6,8 +6,8 @@
  * into work items of one workgroup round, and a scatter of system indices
  * into the bins. The solve is then one launch per size class - classes of
  * sizes with the same register budget, so that each class runs at the
- * occupancy its largest size allows - with one workgroup per work item (the
- * plan gives every workgroup its item), or one launch per size.
+ * occupancy its largest size allows - with one workgroup per work item (in very
+ * large batches a few items per workgroup), or one launch per size.
  *
  * System s: matrix column-major at A + offA[s] (lda = n[s]), right-hand side
  * and pivots at offset offB[s], info[s].
@@ -38,6 +38,12 @@ __host__ __device__ constexpr int ragged_class_waves(int c) { return c == 0 ? 3 
 
 /* grouping kernels: at most this many workgroups of this many threads */
 constexpr int kGroupBlocks = 256, kGroupThreads = 1024;
+
+/* work items a workgroup of a class kernel takes at most. The loop over them
+ * costs class 0 more registers than it has (44 bytes per lane of scratch), and
+ * class 2, whose items hold twice the systems, 2 to 6% also where each
+ * workgroup has one item. */
+__host__ __device__ constexpr int ragged_class_items(int c) { return c == 1 ? 4 : 1; }
 
 struct RaggedPlan {
     int32_t count[33];      /* systems of each size */
@@ -75,8 +81,8 @@ __host__ __device__ constexpr int ragged_per_round(int T)
 
 __host__ __device__ constexpr int ragged_per_item(int T) { return ragged_per_round(T); }
 
-/* LDS doubles of a workgroup: the solver records of its segments, for the
- * size and lane count of LO..HI that takes most */
+/* LDS doubles of a wave: the solver records of its segments, for the size and
+ * lane count of LO..HI that takes most */
 template <int LO, int HI>
 __host__ __device__ constexpr int ragged_lds()
 {
@@ -84,7 +90,7 @@ __host__ __device__ constexpr int ragged_lds()
     if constexpr (LO <= HI) {
         for (int T = 2; T <= 16; T *= 2)
             if (ragged_lanes_ok(LO, T)) {
-                const int d = ragged_per_round(T) * seg_lds<LO>::kStride;
+                const int d = 64 / T * seg_lds<LO>::kStride;
                 most = d > most ? d : most;
             }
         const int rest = ragged_lds<LO + 1, HI>();
@@ -123,10 +129,18 @@ __device__ __forceinline__ int fresh_lane()
     return l;
 }
 
+/* the wave's number in its workgroup (uniform) */
+__device__ __forceinline__ int ragged_wave()
+{
+    return __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+}
+
 /* Solve the cnt (>= 1) systems of one work item with the whole workgroup, T
  * lanes per system (T == 1: one thread per system). Threads or segments
  * without a system point at system 0, load zeros and store nothing. lds: the
- * workgroup's solver records (ragged_lds); W: waves per SIMD of the kernel. */
+ * wave's solver records (ragged_lds), its own whatever the size: the waves of a
+ * workgroup go from item to item without waiting for each other. W: waves per
+ * SIMD of the kernel. */
 template <int N, int T, int W, typename Loc>
 __device__ __forceinline__ void solve_item(const Loc &loc, int cnt, int factors, double *lds)
 {
@@ -167,7 +181,7 @@ __device__ __forceinline__ void solve_item(const Loc &loc, int cnt, int factors,
         constexpr int K = lanes_shape<N, T>::K;
         constexpr bool PF = seg_shape<N, T>::waves(seg_shape<N, T>::kNeed + 28) >= W;
         constexpr int SPW = 64 / T;
-        const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+        const int wave = ragged_wave();
         /* rebuilt after the solve, with the system's pointers, so that neither
          * stays live across it */
         int g, t;
@@ -195,10 +209,10 @@ __device__ __forceinline__ void solve_item(const Loc &loc, int cnt, int factors,
                 x[sl] = ok ? p.b[r] : 0.0;
             });
         }
-        double *rec = lds + (wave * SPW + g) * seg_lds<N>::kStride;
+        double *rec = lds + g * seg_lds<N>::kStride;
         const int inf = seg_getrf_solve<N, T, false, seg_shape<N, T>::CH, PF>(m, x, pos, rec);
         set_geometry();
-        rec = lds + (wave * SPW + g) * seg_lds<N>::kStride;
+        rec = lds + g * seg_lds<N>::kStride;
         if (act) {
             const SysPtrs p = loc.sys(wave * SPW + g);
             const int *seq = reinterpret_cast<const int *>(rec + seg_lds<N>::kPos);
@@ -271,9 +285,9 @@ template <int N>
 __global__ void __launch_bounds__(kRaggedThreads)
     __attribute__((amdgpu_waves_per_eu(ragged_class_waves(ragged_class_of(N))))) k_ragged_one(RaggedArgs a)
 {
-    __shared__ __align__(16) double lds[ragged_lds<N, N>()];
+    __shared__ __align__(16) double lds[kRaggedWaves][ragged_lds<N, N>()];
     const int it = a.plan->item_start[N] + (int)xcd_block(blockIdx.x, gridDim.x);
-    ragged_run_item<N, ragged_class_waves(ragged_class_of(N))>(a, it, lds);
+    ragged_run_item<N, ragged_class_waves(ragged_class_of(N))>(a, it, lds[ragged_wave()]);
 }
 
 template <int N, int W>
@@ -291,31 +305,56 @@ __device__ __forceinline__ void ragged_dispatch(const RaggedArgs &a, int n, int 
     (void)(ragged_try<LO + Ns, W>(a, n, it, lds) || ...);
 }
 
-/* Work item a.item0 + b of class C (sizes LO..HI) by workgroup b, largest sizes
- * first. Workgroups go to the XCDs in turn, so each XCD gets the same mix of
- * sizes: with one contiguous range of items per XCD the first one had all the
- * largest systems. The host does not know how many items a class has, so the grid is the bound
- * that the batch size gives, and workgroups without an item end at once: 0.22 ns
- * each (500000 empty workgroups: 109 us), about 1% of the mixed batch of 2
- * million systems. Walking the items with a resident grid instead costs
- * registers that the solver needs: 36 to 96 bytes per lane of scratch at these
- * occupancies. The size of an item is the smallest m whose first item is at or
- * before it (empty sizes start where the next one does). */
+/* Work item i of class C (sizes LO..HI) in this launch; false past the last.
+ * The size of an item is the smallest m whose first item is at or before it
+ * (empty sizes start where the next one does). */
 template <int C>
-__device__ __forceinline__ void ragged_class_item(const RaggedArgs &a)
+__device__ __forceinline__ bool ragged_class_item(const RaggedArgs &a, int i, double *lds)
 {
     constexpr int LO = ragged_class_lo(C), HI = ragged_class_hi(C);
-    __shared__ __align__(16) double lds[ragged_lds<LO, HI>()];
     const RaggedPlan *plan = a.plan;
     const int c0 = __builtin_amdgcn_readfirstlane(plan->class_start[C] + a.item0);
     const int left = __builtin_amdgcn_readfirstlane(plan->class_start[C + 1] - c0);
-    if ((int)blockIdx.x >= left) return;
-    const int it = c0 + (int)blockIdx.x;
+    if (i >= left) return false;
+    const int it = c0 + i;
     int n = HI;
     for (int m = HI - 1; m >= LO; --m)
         if (plan->item_start[m] <= it) n = m;
     n = __builtin_amdgcn_readfirstlane(n);
     ragged_dispatch<LO, ragged_class_waves(C)>(a, n, it, lds, std::make_integer_sequence<int, HI - LO + 1>{});
+    return true;
+}
+
+/* Work items a.item0 + b, b + G, ... (at most ragged_class_items) of class C by
+ * workgroup b of G, largest sizes first. Neighbouring workgroups go to the XCDs
+ * in turn, so each XCD gets the same mix of sizes: with one contiguous range of
+ * items per XCD the first one had all the largest systems. The host does not
+ * know how many items a class has, so the grid follows the bound that the batch
+ * size gives (ragged_grid), and workgroups without an item end at once.
+ *
+ * Nothing may live across the solves but the item's number: the arguments are
+ * read anew through a pointer the compiler cannot follow, and the kernel that
+ * loops is compiled without the hoisting of constants out of loops (NO_HOIST in
+ * build.py), which kept 41 registers alive across the solve and put 48 bytes per
+ * lane into scratch memory. A second item is slower than a second workgroup all
+ * the same (its loads wait for the first one's stores, which count on the same
+ * counter: 2000000 systems of n = 17..21 2789 against 2956 us): only very large
+ * batches have one. */
+template <int C>
+__device__ __forceinline__ void ragged_class(const RaggedArgs &direct)
+{
+    __shared__ __align__(16) double lds[kRaggedWaves][ragged_lds<ragged_class_lo(C), ragged_class_hi(C)>()];
+    int i = (int)blockIdx.x;
+    if constexpr (ragged_class_items(C) == 1) {
+        (void)ragged_class_item<C>(direct, i, lds[ragged_wave()]);
+    } else {
+#pragma clang loop unroll(disable)
+        for (int r = 0; r < ragged_class_items(C); ++r, i += (int)gridDim.x) {
+            auto args = (const __attribute__((address_space(4))) RaggedArgs *)__builtin_amdgcn_kernarg_segment_ptr();
+            asm volatile("" : "+s"(args));
+            if (!ragged_class_item<C>(*(const RaggedArgs *)args, i, lds[ragged_wave()])) return;
+        }
+    }
 }
 
 /* ------------------------------------------------------------------------ */
@@ -401,19 +440,19 @@ __device__ __forceinline__ void grouped_dispatch(const GroupDesc &g, int n, int 
 
 /* Work item `it` of a grouped launch over the sizes of class C (all threads of
  * the workgroup; items to workgroups in launch order, as in
- * ragged_class_item): find its group (uniform), then solve its systems. */
+ * ragged_class): find its group (uniform), then solve its systems. */
 template <int C>
 __device__ __forceinline__ void grouped_run(const GroupedArgs &a, int it)
 {
     constexpr int LO = ragged_class_lo(C), HI = ragged_class_hi(C);
-    __shared__ __align__(16) double lds[ragged_lds<LO, HI>()];
+    __shared__ __align__(16) double lds[kRaggedWaves][ragged_lds<LO, HI>()];
     int gi = 0;
     for (int k = 1; k < a.ngroups; ++k)
         if (it >= a.g[k].item0) gi = k;
     gi = __builtin_amdgcn_readfirstlane(gi);
     const GroupDesc &g = a.g[gi];
     grouped_dispatch<LO, ragged_class_waves(C)>(g, __builtin_amdgcn_readfirstlane(g.n), it - g.item0,
-                                                g.factors, lds,
+                                                g.factors, lds[ragged_wave()],
                                                 std::make_integer_sequence<int, HI - LO + 1>{});
 }
 

@@ -129,6 +129,20 @@ void ragged_ws_destroy(RaggedWs *ws)
     delete ws;
 }
 
+/* Workgroups for at most `items` work items of class c. A workgroup without an
+ * item costs 0.22 ns, which a batch of small sizes pays for every class it does
+ * not use. Up to kOnePer possible items (14 us) there is a workgroup for each;
+ * beyond, a workgroup takes up to ragged_class_items. 2000000 systems of n = 1 /
+ * 2 / 3 / 2..4, us: ds_bpermute kernels on resident grids 98 / 101 / 130 / 205,
+ * a workgroup for each possible item 121 / 130 / 146 / 213, this 104 / 110 / 127 /
+ * 196; n = 17..21, whose workgroups do take several items, 4370, 2735, 2940. At
+ * 1000000 systems the second form was no slower than the first any more. */
+static unsigned ragged_grid(int c, int64_t items)
+{
+    constexpr int64_t kOnePer = 65536;
+    return (unsigned)(items <= kOnePer ? items : (items + ragged_class_items(c) - 1) / ragged_class_items(c));
+}
+
 int ragged_enqueue(RaggedPlan *plan, int32_t *sorted, const uint8_t *lanes, int64_t batch,
                    const int32_t *n, const int64_t *offA, const int64_t *offB, double *A, double *b,
                    int32_t *ipiv, int32_t *info, bool factors, bool per_size, hipStream_t st)
@@ -142,9 +156,9 @@ int ragged_enqueue(RaggedPlan *plan, int32_t *sorted, const uint8_t *lanes, int6
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_err(e);
     if (!per_size) {
-        /* one workgroup per work item, for as many items as a class can have:
-         * every system in its size with the fewest systems per item, and one
-         * item that is not full per size; in launches of at most kMaxItems */
+        /* for as many items as a class can have: every system in its size with
+         * the fewest systems per item, and one item that is not full per size;
+         * in launches of at most kMaxItems (a multiple of ragged_class_items) */
         constexpr int64_t kMaxItems = (int64_t)1 << 23;
         hipError_t (*const launch[kRaggedClasses])(const RaggedArgs &, unsigned, hipStream_t) = {
             ragged_c0_launch, ragged_c1_launch, ragged_c2_launch};
@@ -155,7 +169,7 @@ int ragged_enqueue(RaggedPlan *plan, int32_t *sorted, const uint8_t *lanes, int6
             const int64_t most = batch / per + (ragged_class_hi(c) - ragged_class_lo(c) + 1);
             for (int64_t i0 = 0; i0 < most && e == hipSuccess; i0 += kMaxItems) {
                 a.item0 = (int32_t)i0;
-                e = launch[c](a, (unsigned)(most - i0 < kMaxItems ? most - i0 : kMaxItems), st);
+                e = launch[c](a, ragged_grid(c, most - i0 < kMaxItems ? most - i0 : kMaxItems), st);
             }
         }
         return hip_err(e);
