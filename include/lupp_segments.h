@@ -9,7 +9,7 @@
  * the ds_bpermute form were multiplies and subtracts of the elimination; the
  * rest chose the pivot, gathered the pivot row and kept the positions, and
  * its two ds_bpermute per broadcast double kept LDS busy half of the time.
- * This form issues 4100:
+ * This form issues 4414 (counted with the factors written):
  *
  *   - The wave's candidates and owners are 64-bit wave masks in SGPRs, kept
  *     by scalar instructions, one mask per row slot. Masked work runs under

@@ -101,8 +101,8 @@ __device__ __forceinline__ void newton_block(const lupp_points &pts, const LawK 
     }
 }
 
-/* Occupancy: 7 unknowns fit 3 waves per SIMD without scratch (152 VGPRs);
- * 13 unknowns take the register file of one wave (408 VGPRs and AGPRs, 432
+/* Occupancy: 7 unknowns fit 3 waves per SIMD without scratch (150 VGPRs);
+ * 13 unknowns take the register file of one wave (406 VGPRs and AGPRs, 434
  * with the tangent) and no scratch. */
 template <int NU>
 constexpr int newton_waves_per_eu() { return NU == 7 ? 3 : 1; }

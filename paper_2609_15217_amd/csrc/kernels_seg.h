@@ -17,9 +17,10 @@
 
 namespace lupp {
 
-/* Register budget of the solve per (n, T): the matrix takes 2*K*n VGPRs, the
- * pivot-row chunks 16 or 32, and about 50 + 10*K more are live in a step. The
- * kernels are compiled for the most waves per SIMD that leaves no scratch
+/* Register budget of the solve per (n, T): the matrix takes 2*K*n VGPRs, one
+ * chunk of 4 columns of the two pivot rows and what else is live in a step
+ * 28 + 6*K (a fit to what the compiler allocates), a second chunk in flight 16
+ * more. The kernels are compiled for the most waves per SIMD that leaves no scratch
  * memory (a spilled n = 32 instance ran at half the speed); chunks of 4
  * columns are fetched ahead where that costs no wave. */
 template <int N, int T>
